@@ -34,8 +34,19 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found; the HIP library cannot be built")
 
 
-def sources():
-    return [os.path.join(CSRC, s) for s in SOURCES if os.path.exists(os.path.join(CSRC, s))]
+# kernels.hip compiles in parts (part 0: everything but the float64 contraction kernels), so that
+# its many template instances build side by side
+F64_PARTS = 6
+
+
+def units():
+    """(source, extra flags, object name) of every compilation; the longest first."""
+    out = []
+    for s in SOURCES:
+        for part in range(F64_PARTS if s == "kernels.hip" else 1):
+            flags = ["-DTAMM_F64_PART=%d" % part] if s == "kernels.hip" else []
+            out.append((os.path.join(CSRC, s), flags, "%s.%d.o" % (s, part)))
+    return sorted(out, key=lambda u: not (u[1] and u[1] != ["-DTAMM_F64_PART=0"]))
 
 
 def build_hip(verbose: bool = False) -> str:
@@ -45,8 +56,8 @@ def build_hip(verbose: bool = False) -> str:
 
     compile_flags = [f for f in HIPCC_FLAGS if f != "-shared"]
     with tempfile.TemporaryDirectory(prefix="tamm_build_") as tmpdir:
-        objs = [os.path.join(tmpdir, os.path.basename(src) + ".o") for src in sources()]
-        cmds = [[hipcc()] + compile_flags + ["-c", "-o", obj, src] for src, obj in zip(sources(), objs)]
+        objs = [os.path.join(tmpdir, name) for _, _, name in units()]
+        cmds = [[hipcc()] + compile_flags + flags + ["-c", "-o", obj, src] for (src, flags, _), obj in zip(units(), objs)]
         if verbose:
             for c in cmds:
                 print(" ".join(c), flush=True)

@@ -104,24 +104,12 @@ int pair_nonzero(const int32_t* t, const int8_t*, int32_t, void* user) {
 }
 
 // Workspace slot of a plan: the largest workspace of any configuration with at most max_splits
-// K splits (the autotuner tries only candidates that fit the slot it is given).  The plan is left
-// in its default configuration.
+// K splits (the autotuner tries only candidates that fit the slot it is given), and of the plan as it is.
 int plan_slot(tamm_plan* p, int max_splits, size_t* bytes) {
-  tamm_plan_stats st{};
-  int rc = tamm_plan_stats_get(p, &st);
+  size_t now = 0;
+  const int rc = tamm_plan_workspace_size(p, &now);
   if (rc != TAMM_OK) return rc;
-  size_t mx = 0, n = 0;
-  if ((rc = tamm_plan_workspace_size(p, &mx)) != TAMM_OK) return rc;
-  int32_t nc = 0;
-  tamm_plan_config_count(p, &nc);
-  for (int c = 0; c < nc; ++c)
-    for (int ks = 1; ks <= max_splits; ks *= 2) {
-      if (tamm_plan_set_config(p, c, ks) != TAMM_OK) continue;
-      tamm_plan_workspace_size(p, &n);
-      mx = std::max(mx, n);
-    }
-  if ((rc = tamm_plan_set_config(p, st.kernel_config, st.k_splits)) != TAMM_OK) return rc;
-  *bytes = align256(mx);
+  *bytes = align256(std::max(now, plan_candidate_workspace(p, max_splits)));
   return TAMM_OK;
 }
 
@@ -236,6 +224,9 @@ extern "C" int tamm_chol_ladder_create(tamm_tensor* r, const tamm_tensor* t, con
   for (auto& s : c->strips) {
     // the pair product has thousands of output tiles per strip: no K splits (their partial tiles
     // would take several times the strip of G); the strip ladders may split
+    tamm_plan_stats st{};
+    if ((rc = tamm_plan_stats_get(s->build, &st)) != TAMM_OK) return rc;
+    if (st.k_splits > 1 && (rc = tamm_plan_set_config(s->build, st.kernel_config, 1)) != TAMM_OK) return rc;
     if ((rc = plan_slot(s->build, 1, &s->sz_build)) != TAMM_OK) return rc;
     if ((rc = plan_slot(s->ladder, 8, &s->sz_ladder)) != TAMM_OK) return rc;
     s->off_build = off;

@@ -4,6 +4,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
 #include "internal.h"
 
 namespace tamm {
@@ -11,6 +14,18 @@ namespace tamm {
 // Largest block the gathers address through one buffer resource (bytes, exclusive): every table
 // sum that involves kTableInvalid lands at or beyond it.
 constexpr int64_t kMaxBlockBytes = (int64_t)kTableInvalid * 8;
+
+// f(0), f(1), ..., f(N - 1) with the index as a compile-time constant
+template <int I>
+using int_c = std::integral_constant<int, I>;
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_each(F& f, std::integer_sequence<int, I...>) {
+  (f(int_c<I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_each(f, std::make_integer_sequence<int, N>{});
+}
 
 // Loads through explicit address spaces: per-lane table reads as global loads (not flat), and
 // wave-uniform descriptor reads as scalar loads from the constant address space (the descriptors
@@ -79,8 +94,8 @@ __device__ __forceinline__ ProblemDesc wave_uniform(const ProblemDesc& d) {
   return u;
 }
 __device__ __forceinline__ WorkItem wave_uniform(const WorkItem& w) {
-  return WorkItem{wave_uniform(w.prob), wave_uniform(w.ob), wave_uniform(w.m0), wave_uniform(w.n0), wave_uniform(w.split),
-                  wave_uniform(w.tile)};
+  return WorkItem{wave_uniform(w.prob), wave_uniform(w.ob),    wave_uniform(w.m0),
+                  wave_uniform(w.n0),   wave_uniform(w.shape), wave_uniform(w.tile)};
 }
 __device__ __forceinline__ OutBlockDesc wave_uniform(const OutBlockDesc& b) {
   OutBlockDesc u;
@@ -190,16 +205,24 @@ struct Gather {
   T ra[AE], rb[BE];                       // element q*V + v: element v of load q
 
   __device__ void init(int t) { tid = t; }
+  // rows and cols: the tile's own extents; what lies past them in the block belongs to other tiles,
+  // is not fetched and reads as zero (the tables' first padding entry, at index mext or next)
   __device__ void setup_pair(const PairDesc& d, const int32_t* pool, const T* A, const T* B, int m0, int n0, int mext,
-                             int next) {
+                             int next, int rows, int cols) {
     a_base = A + d.a_off;
     b_base = B + d.b_off;
     a_bytes = (uint32_t)((int64_t)mext * d.kext * 8);
     b_bytes = (uint32_t)((int64_t)next * d.kext * 8);
 #pragma unroll
-    for (int q = 0; q < A_NR; ++q) a_rt[q] = gload(pool + d.a_tabM + m0 + MA::row(tid, q, 0));
+    for (int q = 0; q < A_NR; ++q) {
+      const int r = MA::row(tid, q, 0);
+      a_rt[q] = gload(pool + d.a_tabM + (r < rows ? m0 + r : mext));
+    }
 #pragma unroll
-    for (int q = 0; q < B_NR; ++q) b_rt[q] = gload(pool + d.b_tabN + n0 + MB::row(tid, q, 0));
+    for (int q = 0; q < B_NR; ++q) {
+      const int r = MB::row(tid, q, 0);
+      b_rt[q] = gload(pool + d.b_tabN + (r < cols ? n0 + r : next));
+    }
   }
   __device__ void load_tables(const PairDesc& d, const int32_t* pool, int kbase) {
 #pragma unroll
@@ -207,21 +230,58 @@ struct Gather {
 #pragma unroll
     for (int q = 0; q < B_NK; ++q) b_kt[q] = gload(pool + d.b_tabK + kbase + MB::k(tid, q, 0));
   }
-  __device__ void load_data() {
+  // load y of the chunk: A's loads, then B's
+  __device__ void load_one(int y) {
     // resources built here from wave-uniform values, so that they live in scalar registers
-    const __amdgpu_buffer_rsrc_t a_rsrc = block_rsrc(a_base, a_bytes);
-    const __amdgpu_buffer_rsrc_t b_rsrc = block_rsrc(b_base, b_bytes);
+    const int q = y < MA::L ? y : y - MA::L;
+    if (y < MA::L)
+      buffer_load_vec<T, V>(block_rsrc(a_base, a_bytes), (uint32_t)(a_rt[MA::ridx(q)] + a_kt[MA::kidx(q)]) * 8u, ra + q * V);
+    else
+      buffer_load_vec<T, V>(block_rsrc(b_base, b_bytes), (uint32_t)(b_rt[MB::ridx(q)] + b_kt[MB::kidx(q)]) * 8u, rb + q * V);
+  }
+  __device__ void load_data() {
 #pragma unroll
-    for (int q = 0; q < MA::L; ++q)
-      buffer_load_vec<T, V>(a_rsrc, (uint32_t)(a_rt[MA::ridx(q)] + a_kt[MA::kidx(q)]) * 8u, ra + q * V);
-#pragma unroll
-    for (int q = 0; q < MB::L; ++q)
-      buffer_load_vec<T, V>(b_rsrc, (uint32_t)(b_rt[MB::ridx(q)] + b_kt[MB::kidx(q)]) * 8u, rb + q * V);
+    for (int y = 0; y < MA::L + MB::L; ++y) load_one(y);
   }
   __device__ int a_lds_row(int e) const { return MA::row(tid, e / V, e % V); }
   __device__ int a_lds_k(int e) const { return MA::k(tid, e / V, e % V); }
   __device__ int b_lds_row(int e) const { return MB::row(tid, e / V, e % V); }
   __device__ int b_lds_k(int e) const { return MB::k(tid, e / V, e % V); }
+};
+
+// Walk of one work item over the chunks of its pairs [pb, pe), KT summed indices each: the
+// bookkeeping that runs ahead of the gathers.
+template <int KT, typename G, typename T>
+struct ChunkWalk {
+  G& g;
+  const PairDesc* pairs;
+  int pe;
+  const int32_t* pool;
+  const T* A;
+  const T* B;
+  const WorkItem& w;
+  int mext, next_;
+  PairDesc d;  // pair of the chunk whose tables were fetched last
+  int p, k;    // its index and that chunk's first summed index
+
+  __device__ __forceinline__ ChunkWalk(G& g_, const PairDesc* pairs_, int pb, int pe_, const int32_t* pool_, const T* A_, const T* B_,
+                                       const WorkItem& w_, int mext_, int nxt)
+      : g(g_), pairs(pairs_), pe(pe_), pool(pool_), A(A_), B(B_), w(w_), mext(mext_), next_(nxt), d(wave_uniform(sload(pairs_ + pb))),
+        p(pb), k(0) {}
+  __device__ __forceinline__ void setup() { g.setup_pair(d, pool, A, B, w.m0, w.n0, mext, next_, shape_rows(w.shape), shape_cols(w.shape)); }
+  // table entries of the next chunk; false past the last one
+  __device__ __forceinline__ bool next_tables() {
+    k += KT;
+    if (k >= d.kext) {
+      ++p;
+      k = 0;
+      if (p >= pe) return false;
+      d = wave_uniform(sload(pairs + p));
+      setup();
+    }
+    g.load_tables(d, pool, k);
+    return true;
+  }
 };
 
 // Chunk pipeline of one work item, shared by the contraction kernels.  LDS holds two chunk
@@ -236,7 +296,7 @@ struct Gather {
 // Chunks run over pairs [pb, pe) and KT-long pieces of each.
 template <int KT, int W, typename G, typename T, typename StoreF, typename ComputeF>
 __device__ __forceinline__ void chunk_pipeline(G& g, const PairDesc* pairs, int pb, int pe, const int32_t* pool,
-                                               const T* A, const T* B, int m0, int n0, int mext, int next,
+                                               const T* A, const T* B, const WorkItem& w, int mext, int next,
                                                StoreF&& store, ComputeF&& compute) {
   PairDesc d1 = wave_uniform(sload(pairs + pb));  // pair of the chunk whose tables were fetched last
   int p1 = pb, k1 = 0;
@@ -255,14 +315,14 @@ __device__ __forceinline__ void chunk_pipeline(G& g, const PairDesc* pairs, int 
       k1 = 0;
       if (p1 >= pe) return false;
       d1 = wave_uniform(sload(pairs + p1));
-      g.setup_pair(d1, pool, A, B, m0, n0, mext, next);
+      g.setup_pair(d1, pool, A, B, w.m0, w.n0, mext, next, shape_rows(w.shape), shape_cols(w.shape));
     }
     g.load_tables(d1, pool, k1);
     push();
     return true;
   };
   // prologue: chunk 0 into buffer 0, chunk 1 in flight, table entries of chunk 2 in flight
-  g.setup_pair(d1, pool, A, B, m0, n0, mext, next);
+  g.setup_pair(d1, pool, A, B, w.m0, w.n0, mext, next, shape_rows(w.shape), shape_cols(w.shape));
   g.load_tables(d1, pool, 0);
   push();
   g.load_data();

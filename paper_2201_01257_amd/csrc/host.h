@@ -19,6 +19,9 @@ int ok();
 // Drops the cached one-shot plans that name tensor t (called when t is destroyed).
 void contract_cache_evict(const tamm_tensor* t);
 
+int contract_workspace_within(tamm_tensor* out, const char* out_lbl, const tamm_tensor* lhs, const char* lhs_lbl,
+                              const tamm_tensor* rhs, const char* rhs_lbl, int32_t precision, size_t limit, size_t* bytes);
+
 // AddOp enqueue (addop.cpp), shared with the scheduler.
 int add_enqueue(tamm_add* a, double alpha, double beta, hipStream_t s);
 const tamm_tensor* add_out(const tamm_add* a);
@@ -32,6 +35,7 @@ int add_chain_enqueue(const std::vector<tamm_add*>& m, const std::vector<double>
 // Plans and groups (plan.cpp), shared with the scheduler.
 void plan_io(const tamm_plan* p, tamm_tensor** out, const tamm_tensor** lhs, const tamm_tensor** rhs, int* precision);
 bool plans_fusable(tamm_plan* a, tamm_plan* b);
+size_t plan_candidate_workspace(const tamm_plan* p, int max_splits);
 int group_create_nodes(const std::vector<std::vector<tamm_plan*>>& nodes, tamm_group** out);
 int group_enqueue(tamm_group* g, hipStream_t s);
 int group_update_desc(tamm_group* g, const double* alpha, const double* beta, hipStream_t s, bool* changed);

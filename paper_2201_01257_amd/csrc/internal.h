@@ -56,14 +56,20 @@ struct WorkItem {
   int32_t ob;     // output block
   int32_t m0;     // first flattened row of the tile
   int32_t n0;     // first flattened column
-  int32_t split;  // split index in bits 0-15, number of splits of the tile in bits 16-30 (0 = 1)
+  int32_t shape;  // split and extents, see item_shape
   int32_t tile;   // first partial-tile slot of the tile (split tiles only)
 };
 static_assert(sizeof(WorkItem) == 24, "WorkItem layout");
 
-__host__ __device__ inline int32_t item_split(const WorkItem& w) { return w.split & 0xFFFF; }
-__host__ __device__ inline int32_t item_nsplit(const WorkItem& w) { return (w.split >> 16) > 1 ? (w.split >> 16) : 1; }
-__host__ __device__ inline int32_t encode_split(int32_t split, int32_t nsplit) { return split | (nsplit << 16); }
+// Split index (bits 0-6), number of splits of the tile (7-13), and the tile's extents less one,
+// rows (14-21) and columns (22-29): at most the configuration's, never past the block.
+__host__ __device__ inline int32_t item_shape(int32_t split, int32_t nsplit, int32_t rows, int32_t cols) {
+  return split | (nsplit << 7) | ((rows - 1) << 14) | ((cols - 1) << 22);
+}
+__host__ __device__ inline int32_t shape_split(int32_t s) { return s & 0x7F; }
+__host__ __device__ inline int32_t shape_nsplit(int32_t s) { return (s >> 7) & 0x7F; }
+__host__ __device__ inline int32_t shape_rows(int32_t s) { return ((s >> 14) & 0xFF) + 1; }
+__host__ __device__ inline int32_t shape_cols(int32_t s) { return ((s >> 22) & 0xFF) + 1; }
 
 // Everything the contraction kernel needs about one contraction.
 struct ProblemDesc {
@@ -86,13 +92,17 @@ struct ProblemDesc {
 };
 static_assert(sizeof(ProblemDesc) == 112, "ProblemDesc layout");
 
+// Queues of a persistent launch, one per accelerator die: the work list is cut into kQueues runs,
+// queue_begin[x] .. queue_begin[x + 1] for die x; a workgroup takes items from its own die's run
+// through that run's counter, then from the others'.
+constexpr int kQueues = 8;
 struct ContractParams {
   ProblemDesc single;         // used when probs is null (one plan)
   const ProblemDesc* probs;   // group: per-problem descriptors in device memory
   const WorkItem* work;
-  int32_t* next_item;         // persistent launch: work counter (starts at gridDim.x), else null
+  int32_t* queue_next;        // persistent launch: items taken from each queue (zero at its start), else null
+  int32_t queue_begin[kQueues + 1];
   int32_t n_work;
-  int32_t pad;
 };
 
 // Screening of one contraction (a segment).  Several contractions that write the same output
@@ -140,7 +150,7 @@ struct ScreenParams {
 struct ReduceItem {
   int32_t prob, ob, m0, n0;
   int32_t tile;    // first partial-tile slot
-  int32_t nsplit;  // partial tiles to sum, in slot order
+  int32_t shape;   // extents and number of partial tiles to sum in slot order (item_shape)
 };
 
 struct ReduceParams {
@@ -229,11 +239,15 @@ hipError_t launch_fill(double* p, int64_t n, double value, hipStream_t s);
 // Kernel configuration of the FP64 contraction kernel family.
 struct F64Config {
   int mt, nt, kt, wgm, wgn, occ;  // occ: minimum waves per SIMD the registers must allow
+  int resident;                   // workgroups that fit on a compute unit (registers and LDS)
+  double tflops;                  // measured on large blocks
   const char* name;
 };
 
 int f64_config_count();
 const F64Config& f64_config(int id);
+// The first configuration with the same kernel as `id` (ids stay valid in saved tuning files).
+int f64_config_canonical(int id);
 
 // Launchers (kernels.hip).  Return hipError_t of the launch.  grid <= 0: one workgroup per item.
 hipError_t launch_screen(const ScreenParams& p, hipStream_t s);
@@ -241,7 +255,7 @@ hipError_t launch_contract_f64(int config, int layout, const ContractParams& p, 
 // Resident workgroups per compute unit of one configuration and gather layout (at least 1).
 int f64_occupancy(int config, int layout);
 hipError_t launch_reduce(const ReduceParams& p, hipStream_t s);
-hipError_t launch_set_counter(int32_t* counter, int32_t value, hipStream_t s);
+hipError_t launch_clear_queues(int32_t* queue_next, hipStream_t s);
 hipError_t launch_denominator(const DenomParams& p, hipStream_t s);
 
 }  // namespace tamm

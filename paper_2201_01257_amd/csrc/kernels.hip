@@ -6,10 +6,17 @@
 #include "device_util.h"
 #include "internal.h"
 
+// Part of the file to compile: 0 = all but the float64 contraction kernels, n = those of
+// TAMM_F64_KERNELS_n (they take most of the compile time and are built side by side).
+#ifndef TAMM_F64_PART
+#define TAMM_F64_PART 0
+#endif
+
 namespace tamm {
 
 typedef double d4_t __attribute__((ext_vector_type(4)));
 
+#if TAMM_F64_PART == 0
 // ---------------------------------------------------------------------------------------------
 // Tile-pair screening (the block non-zero analysis).  One wave per stored output block walks the
 // K tile tuples in lexicographic order, keeps a pair when both operand blocks are stored, and
@@ -76,6 +83,7 @@ hipError_t launch_screen(const ScreenParams& p, hipStream_t s) {
   hipLaunchKernelGGL(k_screen, dim3(p.n_items), dim3(64), 0, s, p);
   return hipGetLastError();
 }
+#endif  // TAMM_F64_PART == 0
 
 // ---------------------------------------------------------------------------------------------
 // FP64 contraction.
@@ -151,314 +159,327 @@ __device__ __forceinline__ void lds_store(double* dst, const double* v) {
   }
 }
 
-template <int MT, int NT, int KT, int WGM, int WGN, int OCC, bool A_KC, bool B_KC, int VEC>
-__global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(OCC))) void k_contract_f64(ContractParams P) {
+// The register that holds the die (XCC) a wave runs on: id 20, offset 0, 4 bits.
+constexpr int kXccIdReg = 20 | (0 << 6) | ((4 - 1) << 11);
+constexpr int min_c(int a, int b) { return a < b ? a : b; }
+
+// One work item whose tile takes FM x FN fragments of 16 x 16 per wave: at most (16 WGM FM) x
+// (16 WGN FN) elements, the last ones possibly past the item's rows or columns.  FMX, FNX: the
+// configuration's largest fragment counts (the layout of the partial tiles).
+template <int FM, int FN, int FMX, int FNX, int KT, int WGM, int WGN, bool A_KC, bool B_KC, int VEC>
+__device__ __forceinline__ void contract_tile(const ProblemDesc& pr, const WorkItem& w, const OutBlockDesc& blk, double* smem) {
   constexpr int NTHR = 64 * WGM * WGN;
-  constexpr int WM = MT / WGM, WN = NT / WGN;
-  constexpr int FM = WM / 16, FN = WN / 16;
+  constexpr int WM = 16 * FM, WN = 16 * FN, MT = WM * WGM, NT = WN * WGN;
+  constexpr int MT_MAX = 16 * FMX * WGM, NT_MAX = 16 * FNX * WGN;
   constexpr int NS = KT / 4;  // MFMA k-steps per chunk
-  static_assert(WM % 16 == 0 && WN % 16 == 0, "wave tile must be a multiple of 16");
-  static_assert(KT % 4 == 0 && NS >= 2, "KT a multiple of 4, at least 8");
-  using G = Gather<MT, NT, KT, NTHR, A_KC, B_KC, double, VEC>;
+  static_assert(KT % 8 == 0, "an even number of k-steps");
+  // 16-byte gathers where this tile's chunks split into them
+  constexpr bool VEC_FITS = gather_pairs_fit<MT, KT, NTHR, A_KC>() && gather_pairs_fit<NT, KT, NTHR, B_KC>();
+  constexpr int V = VEC == 2 && VEC_FITS ? 2 : 1;
+  using G = Gather<MT, NT, KT, NTHR, A_KC, B_KC, double, V>;
   using LA = LdsLayout<MT, KT, A_KC>;
   using LB = LdsLayout<NT, KT, B_KC>;
-  __shared__ __attribute__((aligned(16))) double As[2][LA::SIZE];
-  __shared__ __attribute__((aligned(16))) double Bs[2][LB::SIZE];
-  __shared__ int s_next;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  static_assert(LA::SIZE <= LdsLayout<MT_MAX, KT, A_KC>::SIZE && LB::SIZE <= LdsLayout<NT_MAX, KT, B_KC>::SIZE,
+                "a smaller tile fits the configuration's buffers");
+  double* const As = smem;
+  double* const Bs = smem + 2 * LA::SIZE;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // keeps the addresses of one tile size out of the registers of the others
+  const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WGM, wn = wave / WGM;
   const int lr = lane & 15, lq = lane >> 4;
   const int a_frag = LA::at(wm * WM + lr, lq);  // this lane's operand reads at k-step 0
   const int b_frag = LB::at(wn * WN + lr, lq);
   G g;
   g.init(tid);
+  const int32_t* __restrict__ pool = pr.pool;
+  const PairDesc* __restrict__ pairs = pr.pairs + blk.pair_base;
+  const int cnt = wave_uniform(gload(pr.counts + w.ob));
+  const int nsplit = shape_nsplit(w.shape), split = shape_split(w.shape);
+  const int pb = (int)(((int64_t)cnt * split) / nsplit), pe = (int)(((int64_t)cnt * (split + 1)) / nsplit);
 
-  int item = blockIdx.x;
-  while (item < P.n_work) {
-    // work-item descriptors are the same for the whole wave: keep them in scalar registers
-    const WorkItem w = wave_uniform(sload(P.work + item));
-    const ProblemDesc pr = wave_uniform(P.probs ? sload(P.probs + w.prob) : P.single);
-    const OutBlockDesc blk = wave_uniform(sload(pr.blocks + w.ob));
-    const int32_t* __restrict__ pool = pr.pool;
-    const PairDesc* __restrict__ pairs = pr.pairs + blk.pair_base;
-    const int cnt = wave_uniform(gload(pr.counts + w.ob));
-    const int nsplit = item_nsplit(w), split = item_split(w);
-    const int pb = (int)(((int64_t)cnt * split) / nsplit), pe = (int)(((int64_t)cnt * (split + 1)) / nsplit);
+  d4_t acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = (d4_t){0.0, 0.0, 0.0, 0.0};
 
-    d4_t acc[FM][FN];
+  if (pb < pe) {
+    double af[2][FM], bf[2][FN];  // operands of two k-steps
+    constexpr int NF = FM * FN, NR = FM + FN, AL = G::MA::L, NL = AL + G::MB::L, NP = NF * (NS - 1);
+    constexpr int RPP = (NR + NF - 1) / NF;  // operand reads beside one product
+    // operand r (A fragments, then B fragments) of k-step st of the chunk in buffer b, into set f
+    auto fetch = [&](int b, auto st, auto r, auto f) {
+      if constexpr (r() < FM) af[f()][r()] = As[b * LA::SIZE + a_frag + r() * 16 * LA::RS + 4 * st() * LA::KS];
+      else bf[f()][r() - FM] = Bs[b * LB::SIZE + b_frag + (r() - FM) * 16 * LB::RS + 4 * st() * LB::KS];
+    };
+    // staged load y of the chunk (A's, then B's): to LDS buffer b, and from memory again
+    auto restage = [&](int b, auto y) {
+      constexpr int e = (y() < AL ? y() : y() - AL) * V;
+      if constexpr (y() < AL)
+        lds_store<V, LA::PAIR, LA::STORE16>(&As[b * LA::SIZE + LA::at(g.a_lds_row(e), g.a_lds_k(e))], &g.ra[e]);
+      else
+        lds_store<V, LB::PAIR, LB::STORE16>(&Bs[b * LB::SIZE + LB::at(g.b_lds_row(e), g.b_lds_k(e))], &g.rb[e]);
+      g.load_one(y());
+    };
+    // the operand reads beside product x of a k-step: of k-step st of buffer b, into set f
+    auto fetch_beside = [&](int b, auto st, auto x, auto f) {
+      static_for<RPP>([&](auto q) {
+        if constexpr (x() * RPP + q() < NR) fetch(b, st, int_c<x() * RPP + q()>{}, f);
+      });
+    };
+    ChunkWalk<KT, G, double> walk(g, pairs, pb, pe, pool, pr.A, pr.B, w, blk.mext, blk.next);
+    walk.setup();
+    g.load_tables(walk.d, pool, 0);
+    g.load_data();
+    bool inflight = walk.next_tables();  // the chunk staged during this one is real
+    static_for<NL>([&](auto y) { restage(0, y); });
+    bool tabs = inflight && walk.next_tables();  // so is the one after it
+    __syncthreads();
+    static_for<NR>([&](auto r) { fetch(0, int_c<0>{}, r, int_c<0>{}); });
+    for (int buf = 0;; buf ^= 1) {
+      // Every k-step but the last: beside each product the wave issues a little of what feeds the
+      // later ones -- an operand read of the next k-step, and in the first half now and then the LDS
+      // store of one staged load and the load that refills its registers (early, so that they
+      // arrive before the next chunk stores them).  Left to itself the compiler issues all stores
+      // and loads of the chunk in one run, during which the wave multiplies nothing: dense 4D on
+      // 1024-row blocks 66.0 TF/s, against 69.3 with the stores spread and 70.9 with the barrier
+      // before the last step's products as well (128 x 128 tiles).
+      __builtin_amdgcn_s_setprio(1);  // MFMA phase first when waves of two workgroups compete
+      static_for<NP>([&](auto x) {
+        constexpr int st = x() / NF, i = x() % NF / FN, j = x() % FN;
+        fetch_beside(buf, int_c<st + 1>{}, int_c<x() % NF>{}, int_c<(st + 1) & 1>{});
+        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[st & 1][i], bf[st & 1][j], acc[i][j], 0, 0, 0);
+        constexpr int y0 = min_c(2 * x() * NL / NP, NL), y1 = min_c(2 * (x() + 1) * NL / NP, NL);
+        static_for<y1 - y0>([&](auto y) { restage(buf ^ 1, int_c<y0 + y()>{}); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      // Here every wave holds the operands of the chunk's last k-step and has stored its part of
+      // the next chunk: the buffers change hands, and the next chunk's first operands are read
+      // under the last step's products.
+      __syncthreads();
+      static_for<NF>([&](auto x) {
+        constexpr int i = x() / FN, j = x() % FN;
+        fetch_beside(buf ^ 1, int_c<0>{}, x, int_c<0>{});
+        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[1][i], bf[1][j], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      __builtin_amdgcn_s_setprio(0);
+      const bool tabs_next = tabs && walk.next_tables();
+      if (!inflight) break;
+      inflight = tabs;
+      tabs = tabs_next;
+    }
+  }
+
+  // epilogue: lane holds D[m][n] for m = 4r + lane/16 (register r), n = lane%16
+  const int mb = wm * WM + lq, nb = wn * WN + lr;  // this lane's first row and column in the tile
+  if (nsplit > 1) {
+    double* part = pr.partial + ((int64_t)w.tile + split) * (MT_MAX * NT_MAX);
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
-      for (int j = 0; j < FN; ++j) acc[i][j] = (d4_t){0.0, 0.0, 0.0, 0.0};
-
-    // A tile that runs past its block holds fewer live 16 x 16 output fragments than waves x
-    // fragments per wave.  When dealing the live ones round-robin over the waves (fragment f to
-    // wave f % NW, slot f / NW) shortens the longest wave's share, each wave multiplies only its
-    // dealt fragments: the workgroup's barrier-to-barrier time is set by that longest share.
-    // Every output element is still summed by one wave in the same k order, so the results are
-    // the same bits either way.
-    constexpr int NW = WGM * WGN, NSLOT = FM * FN;
-    const int fml = min(MT / 16, (blk.mext - w.m0 + 15) >> 4), fnl = min(NT / 16, (blk.next - w.n0 + 15) >> 4);
-    const bool dealt = (fml * fnl + NW - 1) / NW < NSLOT;
-    const int wv = wave_uniform(wave);
-    const int nslot = dealt ? max(0, min(NSLOT, (fml * fnl - wv + NW - 1) / NW)) : NSLOT;
-
-    if (pb < pe) {
-      auto store = [&](int b) {
+      for (int j = 0; j < FN; ++j)
 #pragma unroll
-        for (int e = 0; e < G::AE; e += VEC)
-          lds_store<VEC, LA::PAIR, LA::STORE16>(&As[b][LA::at(g.a_lds_row(e), g.a_lds_k(e))], &g.ra[e]);
+        for (int r = 0; r < 4; ++r) part[(mb + i * 16 + 4 * r) * NT_MAX + nb + j * 16] = acc[i][j][r];
+  } else {
+    // through out's offset tables: every table entry first (the tables are padded, so rows and
+    // columns past the block read in bounds), then per row block the old values (beta != 0),
+    // then the results, so that no load waits behind the use of another
+    const double alpha = pr.alpha, beta = pr.beta;
+    __attribute__((address_space(1))) double* __restrict__ Cg = (__attribute__((address_space(1))) double*)pr.C;
+    const int rows = shape_rows(w.shape), cols = shape_cols(w.shape);
+    int32_t rt[FM][4], ct[FN];
 #pragma unroll
-        for (int e = 0; e < G::BE; e += VEC)
-          lds_store<VEC, LB::PAIR, LB::STORE16>(&Bs[b][LB::at(g.b_lds_row(e), g.b_lds_k(e))], &g.rb[e]);
-      };
-      auto compute = [&](int b, bool, auto&& stage, auto&& post) {
-        const double* as = As[b] + a_frag;
-        const double* bs = Bs[b] + b_frag;
-        double af[2][FM], bf[2][FN];
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int i = 0; i < FM; ++i) af[0][i] = as[i * 16 * LA::RS];
+      for (int r = 0; r < 4; ++r) rt[i][r] = gload(pool + blk.c_tabM + w.m0 + mb + i * 16 + 4 * r);
 #pragma unroll
-        for (int j = 0; j < FN; ++j) bf[0][j] = bs[j * 16 * LB::RS];
-        __builtin_amdgcn_s_setprio(1);  // MFMA phase first when waves of two workgroups compete
+    for (int j = 0; j < FN; ++j) ct[j] = gload(pool + blk.c_tabN + w.n0 + nb + j * 16);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const int cur = s & 1, nxt = cur ^ 1;
-          if (s + 1 < NS) {  // operands of the next k-step while this step's MFMAs run
+    for (int i = 0; i < FM; ++i) {
+      double old[4][FN];
 #pragma unroll
-            for (int i = 0; i < FM; ++i) af[nxt][i] = as[i * 16 * LA::RS + 4 * (s + 1) * LA::KS];
+      for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int j = 0; j < FN; ++j) bf[nxt][j] = bs[j * 16 * LB::RS + 4 * (s + 1) * LB::KS];
-          }
-#pragma unroll
-          for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[cur][i], bf[cur][j], acc[i][j], 0, 0, 0);
-          if (s == 0) stage();
+        for (int j = 0; j < FN; ++j) {
+          const bool live = mb + i * 16 + 4 * r < rows && nb + j * 16 < cols;
+          old[r][j] = (beta != 0.0 && live) ? Cg[blk.c_off + rt[i][r] + ct[j]] : 0.0;
         }
-        __builtin_amdgcn_s_setprio(0);
-        post();
-      };
-      if (!dealt) {
-        chunk_pipeline<KT, 0>(g, pairs, pb, pe, pool, pr.A, pr.B, w.m0, w.n0, blk.mext, blk.next, store, compute);
-      } else {
-        // LDS offsets of this wave's dealt fragments: the fragment's first row (the same for the
-        // whole wave) plus the lane's own row and k-step position
-        int sa[NSLOT], sb[NSLOT];
 #pragma unroll
-        for (int q = 0; q < NSLOT; ++q) {
-          const int f = wv + q * NW, fi = f / fnl, fj = f - fi * fnl;
-          sa[q] = wave_uniform(fi * 16 * LA::RS);
-          sb[q] = wave_uniform(fj * 16 * LB::RS);
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          const bool live = mb + i * 16 + 4 * r < rows && nb + j * 16 < cols;
+          const double v = alpha * acc[i][j][r];
+          if (live) Cg[blk.c_off + rt[i][r] + ct[j]] = (beta == 0.0) ? v : beta * old[r][j] + v;
         }
-        auto compute_dealt = [&](int b, bool, auto&& stage, auto&& post) {
-          const double* as = As[b] + LA::at(lr, lq);
-          const double* bs = Bs[b] + LB::at(lr, lq);
-          __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-          for (int s = 0; s < NS; ++s) {
-#pragma unroll
-            for (int q = 0; q < NSLOT; ++q)
-              if (q < nslot)
-                acc[q / FN][q % FN] =
-                    __builtin_amdgcn_mfma_f64_16x16x4f64(as[sa[q] + 4 * s * LA::KS], bs[sb[q] + 4 * s * LB::KS],
-                                                         acc[q / FN][q % FN], 0, 0, 0);
-            if (s == 0) stage();
-          }
-          __builtin_amdgcn_s_setprio(0);
-          post();
-        };
-        chunk_pipeline<KT, 0>(g, pairs, pb, pe, pool, pr.A, pr.B, w.m0, w.n0, blk.mext, blk.next, store, compute_dealt);
-      }
     }
-
-    // epilogue: lane holds D[m][n] for m = 4r + lane/16 (register r), n = lane%16
-    if (dealt) {
-      // per dealt fragment: its rows and columns, then the same writes as below
-      const double alpha = pr.alpha, beta = pr.beta;
-      __attribute__((address_space(1))) double* __restrict__ Cg = (__attribute__((address_space(1))) double*)pr.C;
-#pragma unroll
-      for (int q = 0; q < NSLOT; ++q) {
-        if (q >= nslot) continue;
-        const int f = wv + q * NW, fi = f / fnl, fj = f - fi * fnl;
-        const int n = fj * 16 + lr;
-        if (nsplit > 1) {
-          double* part = pr.partial + ((int64_t)w.tile + split) * (MT * NT);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) part[(fi * 16 + 4 * r + lq) * NT + n] = acc[q / FN][q % FN][r];
-        } else {
-          const int ct = gload(pool + blk.c_tabN + w.n0 + n);
-          int32_t rt[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) rt[r] = gload(pool + blk.c_tabM + w.m0 + fi * 16 + 4 * r + lq);
-          double old[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const bool live = w.m0 + fi * 16 + 4 * r + lq < blk.mext && w.n0 + n < blk.next;
-            old[r] = (beta != 0.0 && live) ? Cg[blk.c_off + rt[r] + ct] : 0.0;
-          }
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const bool live = w.m0 + fi * 16 + 4 * r + lq < blk.mext && w.n0 + n < blk.next;
-            const double v = alpha * acc[q / FN][q % FN][r];
-            if (live) Cg[blk.c_off + rt[r] + ct] = (beta == 0.0) ? v : beta * old[r] + v;
-          }
-        }
-      }
-    } else if (nsplit > 1) {
-      double* part = pr.partial + ((int64_t)w.tile + split) * (MT * NT);
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int m = wm * WM + i * 16 + 4 * r + lq;
-            const int n = wn * WN + j * 16 + lr;
-            part[m * NT + n] = acc[i][j][r];
-          }
-    } else {
-      // through out's offset tables: every table entry first (the tables are padded, so rows and
-      // columns past the block read in bounds), then per row block the old values (beta != 0),
-      // then the results, so that no load waits behind the use of another
-      const double alpha = pr.alpha, beta = pr.beta;
-      __attribute__((address_space(1))) double* __restrict__ Cg = (__attribute__((address_space(1))) double*)pr.C;
-      const int mb = w.m0 + wm * WM + lq, nb = w.n0 + wn * WN + lr;
-      int32_t rt[FM][4], ct[FN];
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) rt[i][r] = gload(pool + blk.c_tabM + mb + i * 16 + 4 * r);
-#pragma unroll
-      for (int j = 0; j < FN; ++j) ct[j] = gload(pool + blk.c_tabN + nb + j * 16);
-#pragma unroll
-      for (int i = 0; i < FM; ++i) {
-        double old[4][FN];
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int j = 0; j < FN; ++j) {
-            const bool live = mb + i * 16 + 4 * r < blk.mext && nb + j * 16 < blk.next;
-            old[r][j] = (beta != 0.0 && live) ? Cg[blk.c_off + rt[i][r] + ct[j]] : 0.0;
-          }
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int j = 0; j < FN; ++j) {
-            const bool live = mb + i * 16 + 4 * r < blk.mext && nb + j * 16 < blk.next;
-            const double v = alpha * acc[i][j][r];
-            if (live) Cg[blk.c_off + rt[i][r] + ct[j]] = (beta == 0.0) ? v : beta * old[r][j] + v;
-          }
-      }
-    }
-    if (!P.next_item) break;
-    __syncthreads();  // s_next is free
-    if (tid == 0) s_next = atomicAdd(P.next_item, 1);
-    __syncthreads();
-    item = s_next;
   }
 }
 
-__global__ void k_set_counter(int32_t* c, int32_t v) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *c = v;
+// The tile body for the item's fragment counts (um x un per wave), each compiled for its own
+// counts: the chunk loop has no branch in its product stream whatever the tile's size.
+template <int FM, int FN, int FMX, int FNX, int KT, int WGM, int WGN, bool A_KC, bool B_KC, int VEC>
+__device__ __forceinline__ void contract_any(int um, int un, const ProblemDesc& pr, const WorkItem& w, const OutBlockDesc& blk,
+                                             double* smem) {
+  if (FN > 1 && un < FN) {
+    if constexpr (FN > 1) contract_any<FM, FN - 1, FMX, FNX, KT, WGM, WGN, A_KC, B_KC, VEC>(um, un, pr, w, blk, smem);
+  } else if (FM > 1 && um < FM) {
+    if constexpr (FM > 1) contract_any<FM - 1, FN, FMX, FNX, KT, WGM, WGN, A_KC, B_KC, VEC>(um, FN, pr, w, blk, smem);
+  } else {
+    contract_tile<FM, FN, FMX, FNX, KT, WGM, WGN, A_KC, B_KC, VEC>(pr, w, blk, smem);
+  }
 }
 
-hipError_t launch_set_counter(int32_t* counter, int32_t value, hipStream_t s) {
-  hipLaunchKernelGGL(k_set_counter, dim3(1), dim3(64), 0, s, counter, value);
+template <int MT, int NT, int KT, int WGM, int WGN, int OCC, bool A_KC, bool B_KC, int VEC>
+__global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(OCC))) void k_contract_f64(ContractParams P) {
+  constexpr int FM = MT / WGM / 16, FN = NT / WGN / 16;
+  static_assert(MT == FM * WGM * 16 && NT == FN * WGN * 16, "wave tile must be a multiple of 16");
+  __shared__ __attribute__((aligned(16))) double smem[2 * (LdsLayout<MT, KT, A_KC>::SIZE + LdsLayout<NT, KT, B_KC>::SIZE)];
+  __shared__ int s_next;
+  // A launch with one workgroup per item runs its own; a persistent one takes items from its die's
+  // queue and, when that is empty, from the queue with the most items left (counters only grow, so
+  // every workgroup ends).
+  const bool queued = P.queue_next != nullptr;
+  int queue = queued ? (int)__builtin_amdgcn_s_getreg(kXccIdReg) & (kQueues - 1) : 0;
+  int item = blockIdx.x;
+  while (true) {
+    if (queued) {
+      __syncthreads();  // s_next and the tile buffers are free
+      if (threadIdx.x < kQueues) {  // one lane per queue
+        const int lane = threadIdx.x, begin = P.queue_begin[lane], len = P.queue_begin[lane + 1] - begin;
+        int found = -1;
+        while (true) {
+          int i = len;
+          if (lane == queue && len > 0) i = atomicAdd(P.queue_next + lane, 1);
+          found = __shfl(i < len ? begin + i : -1, queue);
+          if (found >= 0) break;
+          const int left = len - __hip_atomic_load(P.queue_next + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          int most = left;
+#pragma unroll
+          for (int o = kQueues / 2; o > 0; o /= 2) most = max(most, __shfl_xor(most, o));
+          if (most <= 0) break;  // nothing is left anywhere
+          queue = __ffsll(__ballot(left == most)) - 1;
+        }
+        if (lane == 0) s_next = found;
+      }
+      queue = __shfl(queue, 0);
+      __syncthreads();
+      item = s_next;
+      if (item < 0) break;
+    } else if (item >= P.n_work) {
+      break;
+    }
+    // work-item descriptors are the same for the whole wave: keep them in scalar registers
+    const WorkItem w = wave_uniform(sload(P.work + wave_uniform(item)));
+    const ProblemDesc pr = wave_uniform(P.probs ? sload(P.probs + w.prob) : P.single);
+    const OutBlockDesc blk = wave_uniform(sload(pr.blocks + w.ob));
+    contract_any<FM, FN, FM, FN, KT, WGM, WGN, A_KC, B_KC, VEC>((shape_rows(w.shape) + 16 * WGM - 1) / (16 * WGM),
+                                                                 (shape_cols(w.shape) + 16 * WGN - 1) / (16 * WGN), pr, w, blk,
+                                                                 smem);
+    if (!queued) break;
+  }
+}
+
+#if TAMM_F64_PART == 0
+__global__ void k_clear_queues(int32_t* queue_next) {
+  if (threadIdx.x < kQueues) queue_next[threadIdx.x] = 0;
+}
+
+hipError_t launch_clear_queues(int32_t* queue_next, hipStream_t s) {
+  hipLaunchKernelGGL(k_clear_queues, dim3(1), dim3(64), 0, s, queue_next);
   return hipGetLastError();
 }
 
 // Ordered reduction of K-split partial tiles (split 0, 1, ... in order) and the epilogue.  A
-// thread takes kReduceUnroll elements at a time and issues all their loads (table entries, then
-// the partials and old values) before any use.
-constexpr int kReduceUnroll = 4;
+// workgroup takes kReduceUnroll elements per thread of one tile (grid: tiles x parts of a tile) and
+// issues all their loads (table entries, then the partials and old values) before any use.  A
+// workgroup per tile walked its 4096 elements four rounds one after another, each a memory round
+// trip: 10.7 us for 96 tiles of 25 x 25, six splits.
+constexpr int kReduceUnroll = 4, kReduceThreads = 256;
 
-__global__ __launch_bounds__(256) void k_reduce(ReduceParams P) {
+__global__ __launch_bounds__(kReduceThreads) void k_reduce(ReduceParams P) {
   const int t = blockIdx.x;
   if (t >= P.n_items) return;
   const ReduceItem it = P.items[t];
+  const int rows = shape_rows(it.shape), cols = shape_cols(it.shape), nsplit = shape_nsplit(it.shape);
+  const int e0 = (int)blockIdx.y * kReduceUnroll * kReduceThreads + (int)threadIdx.x;
+  if (e0 >= rows * cols) return;
   const ProblemDesc& pr = P.probs ? P.probs[it.prob] : P.single;
   const OutBlockDesc blk = pr.blocks[it.ob];
   const int tile = P.tile_m * P.tile_n;
   const double* part = pr.partial + (int64_t)it.tile * tile;
   const double alpha = pr.alpha, beta = pr.beta;
   __attribute__((address_space(1))) double* __restrict__ Cg = (__attribute__((address_space(1))) double*)pr.C;
-  for (int e0 = threadIdx.x; e0 < tile; e0 += kReduceUnroll * blockDim.x) {
-    int64_t idx[kReduceUnroll];
-    bool live[kReduceUnroll];
+  int64_t idx[kReduceUnroll];
+  int src[kReduceUnroll];
+  bool live[kReduceUnroll];
 #pragma unroll
-    for (int u = 0; u < kReduceUnroll; ++u) {
-      const int e = e0 + u * blockDim.x;
-      const int m = it.m0 + e / P.tile_n, n = it.n0 + e % P.tile_n;
-      live[u] = e < tile && m < blk.mext && n < blk.next;
-      idx[u] = live[u] ? blk.c_off + pr.pool[blk.c_tabM + m] + pr.pool[blk.c_tabN + n] : 0;
-    }
-    double s[kReduceUnroll], old[kReduceUnroll];
+  for (int u = 0; u < kReduceUnroll; ++u) {
+    const int e = e0 + u * kReduceThreads, m = e / cols, n = e - m * cols;
+    live[u] = e < rows * cols;
+    src[u] = live[u] ? m * P.tile_n + n : 0;
+    idx[u] = live[u] ? blk.c_off + pr.pool[blk.c_tabM + it.m0 + m] + pr.pool[blk.c_tabN + it.n0 + n] : 0;
+  }
+  double s[kReduceUnroll], old[kReduceUnroll];
 #pragma unroll
-    for (int u = 0; u < kReduceUnroll; ++u) {
-      old[u] = (beta != 0.0 && live[u]) ? Cg[idx[u]] : 0.0;
-      s[u] = 0.0;
-    }
-    for (int k = 0; k < it.nsplit; ++k) {  // split order; the elements' loads of one split together
+  for (int u = 0; u < kReduceUnroll; ++u) {
+    old[u] = (beta != 0.0 && live[u]) ? Cg[idx[u]] : 0.0;
+    s[u] = 0.0;
+  }
+#pragma unroll 4
+  for (int k = 0; k < nsplit; ++k) {  // split order; the elements' loads of one split together
 #pragma unroll
-      for (int u = 0; u < kReduceUnroll; ++u) {
-        const int e = e0 + u * blockDim.x;
-        s[u] += live[u] ? part[(int64_t)k * tile + e] : 0.0;
-      }
-    }
+    for (int u = 0; u < kReduceUnroll; ++u) s[u] += part[(int64_t)k * tile + src[u]];
+  }
 #pragma unroll
-    for (int u = 0; u < kReduceUnroll; ++u) {
-      const double v = alpha * s[u];
-      if (live[u]) Cg[idx[u]] = (beta == 0.0) ? v : beta * old[u] + v;
-    }
+  for (int u = 0; u < kReduceUnroll; ++u) {
+    const double v = alpha * s[u];
+    if (live[u]) Cg[idx[u]] = (beta == 0.0) ? v : beta * old[u] + v;
   }
 }
 
 hipError_t launch_reduce(const ReduceParams& p, hipStream_t s) {
   if (p.n_items <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_reduce, dim3(p.n_items), dim3(256), 0, s, p);
+  const int per = kReduceUnroll * kReduceThreads, parts = (p.tile_m * p.tile_n + per - 1) / per;
+  hipLaunchKernelGGL(k_reduce, dim3(p.n_items, parts), dim3(kReduceThreads), 0, s, p);
   return hipGetLastError();
 }
+#endif  // TAMM_F64_PART == 0
 
 // ---------------------------------------------------------------------------------------------
-// Configurations and dispatch.  X(id, MT, NT, KT, WGM, WGN, OCC): OCC is the minimum number of
-// waves per SIMD the register allocation must allow (1 = no constraint).
+// Configurations and dispatch.  X(kernel, MT, NT, KT, WGM, WGN, OCC, RES, TF): OCC is the minimum number
+// of waves per SIMD the register allocation must allow (1 = no constraint), RES the workgroups that
+// then fit on a compute unit, TF the TFLOP/s measured on large blocks (dense 4D, extents of 128 in
+// tiles of 32).  This file is compiled once for part 0 (everything but these kernels) and once for
+// every other part, a few kernels each.
 // ---------------------------------------------------------------------------------------------
-#define TAMM_F64_CONFIGS(X)            \
-  X(0, 64, 64, 16, 2, 2, 1)            \
-  X(1, 128, 64, 16, 2, 2, 1)           \
-  X(2, 64, 128, 16, 2, 2, 1)           \
-  X(3, 128, 128, 16, 2, 2, 1)          \
-  X(4, 32, 64, 16, 2, 2, 1)            \
-  X(5, 128, 80, 16, 4, 1, 1)           \
-  X(6, 80, 128, 16, 1, 4, 1)           \
-  X(7, 64, 80, 16, 4, 1, 1)            \
-  X(8, 32, 256, 16, 1, 4, 1)           \
-  X(9, 256, 32, 16, 4, 1, 1)           \
-  X(10, 128, 128, 32, 2, 2, 1)         \
-  X(11, 128, 80, 32, 4, 1, 1)          \
-  X(12, 64, 80, 32, 4, 1, 1)           \
-  X(13, 64, 64, 32, 2, 2, 1)           \
-  X(14, 128, 128, 16, 2, 2, 2)
+#define TAMM_F64_KERNELS_1(X) X(m128n128k16, 128, 128, 16, 2, 2, 2, 2, 70.0)
+#define TAMM_F64_KERNELS_2(X) X(m128n64k16, 128, 64, 16, 2, 2, 1, 2, 63.0)
+#define TAMM_F64_KERNELS_3(X) X(m64n128k16, 64, 128, 16, 2, 2, 1, 2, 62.0)
+#define TAMM_F64_KERNELS_4(X)          \
+  X(m64n64k16, 64, 64, 16, 2, 2, 1, 4, 57.0)    \
+  X(m32n64k16, 32, 64, 16, 2, 2, 1, 5, 47.0)    \
+  X(m32n32k16, 32, 32, 16, 1, 1, 1, 8, 46.0)
+#define TAMM_F64_KERNELS_5(X)          \
+  X(m64n80k32, 64, 80, 32, 4, 1, 1, 2, 56.5)    \
+  X(m64n64k32, 64, 64, 32, 2, 2, 1, 2, 57.0)
+#define TAMM_F64_KERNELS(X) \
+  TAMM_F64_KERNELS_1(X) TAMM_F64_KERNELS_2(X) TAMM_F64_KERNELS_3(X) TAMM_F64_KERNELS_4(X) TAMM_F64_KERNELS_5(X)
 
-#define TAMM_CFG_ENTRY(id, mt, nt, kt, wgm, wgn, occ) \
-  {mt, nt, kt, wgm, wgn, occ, "f64_m" #mt "n" #nt "k" #kt "_w" #wgm "x" #wgn "_o" #occ},
-static const F64Config kF64Configs[] = {TAMM_F64_CONFIGS(TAMM_CFG_ENTRY)};
-#undef TAMM_CFG_ENTRY
+#define TAMM_F64_DECLARE(k, mt, nt, kt, wgm, wgn, occ, res, tf)                                           \
+  hipError_t f64_launch_##k(int layout, const ContractParams& p, int grid, hipStream_t s);       \
+  int f64_resident_##k(int layout);
+TAMM_F64_KERNELS(TAMM_F64_DECLARE)
+#undef TAMM_F64_DECLARE
 
-int f64_config_count() { return (int)(sizeof(kF64Configs) / sizeof(kF64Configs[0])); }
-const F64Config& f64_config(int id) { return kF64Configs[id]; }
-
+#if TAMM_F64_PART > 0
 // Gather layout index: bit 1 = A k-contiguous, bit 0 = B k-contiguous, bit 2 = 16-byte gathers.
-// A tile shape whose chunks do not split into pairs runs the 8-byte gather for bit 2 as well.
+// A tile whose chunks do not split into pairs runs the 8-byte gather for bit 2 as well.
 template <int MT, int NT, int KT, int WGM, int WGN, int OCC, int LAYOUT>
 static constexpr auto contract_kernel() {
-  constexpr bool akc = (LAYOUT & 2) != 0, bkc = (LAYOUT & 1) != 0;
-  constexpr int nthr = 64 * WGM * WGN;
-  constexpr bool pairs = (LAYOUT & 4) != 0 && gather_pairs_fit<MT, KT, nthr, akc>() && gather_pairs_fit<NT, KT, nthr, bkc>();
-  return k_contract_f64<MT, NT, KT, WGM, WGN, OCC, akc, bkc, pairs ? 2 : 1>;
+  return k_contract_f64<MT, NT, KT, WGM, WGN, OCC, (LAYOUT & 2) != 0, (LAYOUT & 1) != 0, (LAYOUT & 4) != 0 ? 2 : 1>;
 }
 
 template <int MT, int NT, int KT, int WGM, int WGN, int OCC>
@@ -471,41 +492,56 @@ static auto contract_kernel_for(int layout) {
   return table[layout & 7];
 }
 
-template <int MT, int NT, int KT, int WGM, int WGN, int OCC>
-static hipError_t launch_cfg(int layout, const ContractParams& p, int grid, hipStream_t s) {
-  const dim3 g(grid > 0 ? grid : p.n_work), b(64 * WGM * WGN);
-  const auto kernel = contract_kernel_for<MT, NT, KT, WGM, WGN, OCC>(layout);
-  hipLaunchKernelGGL(kernel, g, b, 0, s, p);
-  return hipGetLastError();
-}
-
-template <int MT, int NT, int KT, int WGM, int WGN, int OCC>
-static int occupancy_cfg(int layout) {
-  int n = 0;
-  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      &n, contract_kernel_for<MT, NT, KT, WGM, WGN, OCC>(layout), 64 * WGM * WGN, 0);
-  return e == hipSuccess && n > 0 ? n : 1;
-}
-
-int f64_occupancy(int config, int layout) {
-  switch (config) {
-#define TAMM_CFG_OCC(id, mt, nt, kt, wgm, wgn, occ) \
-  case id: return occupancy_cfg<mt, nt, kt, wgm, wgn, occ>(layout);
-    TAMM_F64_CONFIGS(TAMM_CFG_OCC)
-#undef TAMM_CFG_OCC
-    default: return 1;
+#define TAMM_F64_DEFINE(k, mt, nt, kt, wgm, wgn, occ, res, tf)                                                               \
+  hipError_t f64_launch_##k(int layout, const ContractParams& p, int grid, hipStream_t s) {                         \
+    const auto kernel = contract_kernel_for<mt, nt, kt, wgm, wgn, occ>(layout);                                     \
+    hipLaunchKernelGGL(kernel, dim3(grid > 0 ? grid : p.n_work), dim3(64 * wgm * wgn), 0, s, p);                    \
+    return hipGetLastError();                                                                                       \
+  }                                                                                                                 \
+  int f64_resident_##k(int layout) {                                                                                \
+    int n = 0;                                                                                                      \
+    const auto kernel = contract_kernel_for<mt, nt, kt, wgm, wgn, occ>(layout);                                     \
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, 64 * wgm * wgn, 0);               \
+    return e == hipSuccess && n > 0 ? n : 1;                                                                        \
   }
+#define TAMM_F64_PART_KERNELS_(n) TAMM_F64_KERNELS_##n
+#define TAMM_F64_PART_KERNELS(n) TAMM_F64_PART_KERNELS_(n)
+TAMM_F64_PART_KERNELS(TAMM_F64_PART)(TAMM_F64_DEFINE)
+#endif  // TAMM_F64_PART > 0
+
+#if TAMM_F64_PART == 0
+struct F64Kernel {
+  F64Config cfg;
+  hipError_t (*launch)(int layout, const ContractParams& p, int grid, hipStream_t s);
+  int (*resident)(int layout);
+};
+#define TAMM_F64_ENTRY(k, mt, nt, kt, wgm, wgn, occ, res, tf)                                                       \
+  static const F64Kernel kF64_##k = {{mt, nt, kt, wgm, wgn, occ, res, tf, "f64_" #k "_w" #wgm "x" #wgn "_o" #occ}, \
+                                     f64_launch_##k, f64_resident_##k};
+TAMM_F64_KERNELS(TAMM_F64_ENTRY)
+#undef TAMM_F64_ENTRY
+
+// Configuration ids, as tuning files hold them.  Ids whose own tile shape became a size of another
+// kernel's tiles (80 and 256 wide, 128 x 128 at one wave per SIMD) name the kernel that runs them.
+static const F64Kernel* const kF64Configs[] = {
+    &kF64_m64n64k16,  &kF64_m128n64k16, &kF64_m64n128k16, &kF64_m128n128k16, &kF64_m32n64k16,
+    &kF64_m128n64k16, &kF64_m64n128k16, &kF64_m64n64k16,  &kF64_m64n128k16,  &kF64_m128n64k16,
+    &kF64_m32n32k16,  &kF64_m128n64k16, &kF64_m64n80k32,  &kF64_m64n64k32,   &kF64_m128n128k16};
+
+int f64_config_count() { return (int)(sizeof(kF64Configs) / sizeof(kF64Configs[0])); }
+const F64Config& f64_config(int id) { return kF64Configs[id]->cfg; }
+int f64_config_canonical(int id) {
+  int c = 0;
+  while (kF64Configs[c] != kF64Configs[id]) ++c;
+  return c;
 }
+
+int f64_occupancy(int config, int layout) { return kF64Configs[config]->resident(layout); }
 
 hipError_t launch_contract_f64(int config, int layout, const ContractParams& p, int grid, hipStream_t s) {
   if (p.n_work <= 0) return hipSuccess;
-  switch (config) {
-#define TAMM_CFG_LAUNCH(id, mt, nt, kt, wgm, wgn, occ) \
-  case id: return launch_cfg<mt, nt, kt, wgm, wgn, occ>(layout, p, grid, s);
-    TAMM_F64_CONFIGS(TAMM_CFG_LAUNCH)
-#undef TAMM_CFG_LAUNCH
-    default: return hipErrorInvalidValue;
-  }
+  if (config < 0 || config >= f64_config_count()) return hipErrorInvalidValue;
+  return kF64Configs[config]->launch(layout, p, grid, s);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -599,5 +635,7 @@ hipError_t launch_denominator(const DenomParams& p, hipStream_t s) {
   }
   return hipGetLastError();
 }
+
+#endif  // TAMM_F64_PART == 0
 
 }  // namespace tamm

@@ -269,8 +269,8 @@ hipError_t launch_prep_split(const PrepParams& p, bool rows_along_lanes, hipStre
 template <int MT, int NT, int WM, int WN, int FM, int FN>
 __device__ __forceinline__ void epilogue_f32layout(const ProblemDesc& pr, const WorkItem& w, const OutBlockDesc& blk,
                                                    d4_t (&acc)[FM][FN], int wm, int wn, int lr, int lq) {
-  if (item_nsplit(w) > 1) {
-    double* part = pr.partial + ((int64_t)w.tile + item_split(w)) * (MT * NT);
+  if (shape_nsplit(w.shape) > 1) {
+    double* part = pr.partial + ((int64_t)w.tile + shape_split(w.shape)) * (MT * NT);
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -337,7 +337,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_contract_f32(ContractParams 
   const int32_t* __restrict__ pool = pr.pool;
   const PairDesc* __restrict__ pairs = pr.pairs + blk.pair_base;
   const int cnt = wave_uniform(gload(pr.counts + w.ob));
-  const int nsplit = item_nsplit(w), split = item_split(w);
+  const int nsplit = shape_nsplit(w.shape), split = shape_split(w.shape);
   const int pb = (int)(((int64_t)cnt * split) / nsplit), pe = (int)(((int64_t)cnt * (split + 1)) / nsplit);
   G g;
   g.init(tid);
@@ -396,7 +396,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_contract_f32(ContractParams 
             }
       }
     };
-    chunk_pipeline<KT, kSplitWindow>(g, pairs, pb, pe, pool, pr.A, pr.B, w.m0, w.n0, blk.mext, blk.next, store, compute);
+    chunk_pipeline<KT, kSplitWindow>(g, pairs, pb, pe, pool, pr.A, pr.B, w, blk.mext, blk.next, store, compute);
   }
   epilogue_f32layout<MT, NT, WM, WN, FM, FN>(pr, w, blk, acc, wm, wn, lr, lq);
 }
@@ -443,7 +443,7 @@ struct PlaneGather {
     b_plane = bp;
   }
   __device__ void setup_pair(const PairDesc& d, const int32_t*, const __bf16* A, const __bf16* B, int m0_, int n0_,
-                             int mext_, int next_) {
+                             int mext_, int next_, int, int) {
     a_base = A + d.a_off;
     b_base = B + d.b_off;
     m0 = m0_;
@@ -523,7 +523,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_contract_bf16s(ContractParam
   const E* Ap = reinterpret_cast<const E*>(pr.A);
   const E* Bp = reinterpret_cast<const E*>(pr.B);
   const int cnt = wave_uniform(gload(pr.counts + w.ob));
-  const int nsplit = item_nsplit(w), split = item_split(w);
+  const int nsplit = shape_nsplit(w.shape), split = shape_split(w.shape);
   const int pb = (int)(((int64_t)cnt * split) / nsplit), pe = (int)(((int64_t)cnt * (split + 1)) / nsplit);
   G g;
   if constexpr (PLANES) g.init(tid, pr.a_plane, pr.b_plane);
@@ -631,7 +631,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_contract_bf16s(ContractParam
             }
       }
     };
-    chunk_pipeline<KT, kSplitWindow>(g, pairs, pb, pe, pool, Ap, Bp, w.m0, w.n0, blk.mext, blk.next, store, compute);
+    chunk_pipeline<KT, kSplitWindow>(g, pairs, pb, pe, pool, Ap, Bp, w, blk.mext, blk.next, store, compute);
   }
   epilogue_f32layout<MT, NT, WM, WN, FM, FN>(pr, w, blk, acc, wm, wn, lr, lq);
 }

@@ -34,7 +34,7 @@ extern "C" int tamm_contract_noalloc(tamm_tensor* out, const char* out_lbl, cons
                                      double beta, void* stream) {
   // the plan (host analysis, cached in the library) fixes the workspace the contraction needs
   size_t need = 0;
-  int rc = tamm_contract_workspace_size(out, out_lbl, lhs, lhs_lbl, rhs, rhs_lbl, precision, &need);
+  int rc = contract_workspace_within(out, out_lbl, lhs, lhs_lbl, rhs, rhs_lbl, precision, kScratchBytes, &need);
   if (rc != TAMM_OK) return rc;
   if (need > kScratchBytes)
     return fail(TAMM_ERR_WORKSPACE,

@@ -85,6 +85,35 @@ struct Layout {
 
 }  // namespace
 
+namespace {
+
+// What the choice of a configuration needs of an output block: extents, surviving pairs, their
+// summed K extent, and the chunks of 16 and of 32 summed indices that they take.
+struct BlockShape {
+  int64_t mext = 0, next = 0, pairs = 0, chunks16 = 0, chunks32 = 0;
+  double kext = 0;
+  int64_t count = 1;  // blocks of this shape
+  bool same(const BlockShape& o) const {
+    return mext == o.mext && next == o.next && pairs == o.pairs && chunks16 == o.chunks16 && chunks32 == o.chunks32 && kext == o.kext;
+  }
+  bool operator<(const BlockShape& o) const {
+    return std::tie(mext, next, pairs, chunks16, chunks32, kext) < std::tie(o.mext, o.next, o.pairs, o.chunks16, o.chunks32, o.kext);
+  }
+};
+
+// Equal shapes together.
+void merge_shapes(std::vector<BlockShape>& v) {
+  std::sort(v.begin(), v.end());
+  size_t n = 0;
+  for (size_t i = 0; i < v.size(); ++i) {
+    if (n > 0 && v[n - 1].same(v[i])) v[n - 1].count += v[i].count;
+    else v[n++] = v[i];
+  }
+  v.resize(n);
+}
+
+}  // namespace
+
 struct tamm_plan {
   tamm_tensor* out = nullptr;
   const tamm_tensor* lhs = nullptr;
@@ -104,6 +133,8 @@ struct tamm_plan {
   int64_t n_kt = 1;
   std::vector<OutBlockDesc> blocks;
   std::vector<double> block_cost;  // sum of K extents of the surviving pairs of each block
+  std::vector<BlockShape> block_shapes;  // of each block
+  std::vector<BlockShape> shapes;  // the distinct ones and how many blocks have each
   uint64_t signature = 0;
   // split-bfloat16 precisions: per stored operand block, the split work description
   std::vector<PrepBlock> prepA, prepB;
@@ -119,11 +150,15 @@ struct tamm_plan {
   int xcd_chunk = -1;              // work items per die chunk (xcd_order); -1: the library default
   int tile_order = 0;              // 0: tiles of a block row by row; 1: grouped by B column panel
   std::vector<WorkItem> work;
+  bool queued = false;             // persistent launch over the dies' queues (float64, more items than resident workgroups)
+  bool no_queue = false;           // never (tamm_contract_noalloc keeps its workspace as small as it was)
+  int32_t queue_begin[kQueues + 1] = {};
+  int queue_slot = 0;              // counter set of the next launch, round robin
   std::vector<ReduceItem> reduce;
   tamm_plan_stats stats{};
   // workspace: static layout, then work list, reduce list, partial tiles
   Layout lay;
-  size_t off_work = 0, off_reduce = 0, off_partial = 0, off_prepA = 0, off_prepB = 0, off_xA = 0, off_xB = 0, ws_size = 0;
+  size_t off_work = 0, off_reduce = 0, off_queue = 0, off_partial = 0, off_prepA = 0, off_prepB = 0, off_xA = 0, off_xB = 0, ws_size = 0;
   char* ws = nullptr;
   size_t ws_bytes = 0;
   bool ws_bound = false;
@@ -139,6 +174,8 @@ static int gather_layout(const tamm_plan* p) {
   return 2 * (p->a_kc ? 1 : 0) + (p->b_kc ? 1 : 0) + (p->pairs ? 4 : 0) + (p->planes ? 8 : 0);
 }
 constexpr int kLayouts = 8;
+constexpr int kComputeUnits = 256;  // MI355X
+constexpr int kQueueSlots = 8;      // counter sets of a plan's persistent launches
 
 static Layout make_layout(const tamm_plan* p, size_t base) {
   Layout L;
@@ -416,6 +453,7 @@ extern "C" int tamm_plan_create(tamm_tensor* out, const char* out_lbl, const tam
   p->block_cost.assign(nob, 0.0);
   double flops = 0;
   int64_t tasks = 0;
+  p->shapes.resize(nob);
   for (int64_t b = 0; b < nob; ++b) {
     const int32_t* ot = &out->block_tiles[b * out->rank];
     OutBlockDesc& d = p->blocks[b];
@@ -460,9 +498,18 @@ extern "C" int tamm_plan_create(tamm_tensor* out, const char* out_lbl, const tam
         ++tasks;
         flops += 2.0 * (double)mext * (double)next * (double)kext;
         p->block_cost[b] += (double)kext;
+        BlockShape& sh = p->shapes[b];
+        ++sh.pairs;
+        sh.chunks16 += (kext + 15) / 16;
+        sh.chunks32 += (kext + 31) / 32;
       }
     }
+    p->shapes[b].mext = mext;
+    p->shapes[b].next = next;
+    p->shapes[b].kext = p->block_cost[b];
   }
+  p->block_shapes = p->shapes;
+  merge_shapes(p->shapes);
   // dropped pairs: surviving pairs whose output block is not stored (user predicates only)
   int64_t dropped = 0;
   {
@@ -518,6 +565,9 @@ extern "C" int tamm_plan_create(tamm_tensor* out, const char* out_lbl, const tam
 // Kernel configuration tables by precision.
 struct TileCfg {
   int mt, nt, kt, threads;
+  int um, un;  // rows and columns of one step of the tile size (16 per wave along the dimension)
+  int resident;  // workgroups that fit on a compute unit
+  double rate;   // flop/s of the whole chip on large blocks
   const char* name;
 };
 
@@ -526,10 +576,10 @@ static int cfg_count(int prec) { return prec == TAMM_PREC_F64 ? f64_config_count
 static TileCfg cfg_get(int prec, int c) {
   if (prec == TAMM_PREC_F64) {
     const F64Config& f = f64_config(c);
-    return TileCfg{f.mt, f.nt, f.kt, 64 * f.wgm * f.wgn, f.name};
+    return TileCfg{f.mt, f.nt, f.kt, 64 * f.wgm * f.wgn, 16 * f.wgm, 16 * f.wgn, f.resident, f.tflops * 1e12, f.name};
   }
   const MixedConfig& f = mixed_config(prec, c);
-  return TileCfg{f.mt, f.nt, f.kt, 64 * f.wgm * f.wgn, f.name};
+  return TileCfg{f.mt, f.nt, f.kt, 64 * f.wgm * f.wgn, f.mt, f.nt, 1, 1e14, f.name};
 }
 
 // Number of output tiles and padding factor of one configuration.
@@ -546,15 +596,15 @@ static std::pair<int64_t, double> tiles_for(const tamm_plan* p, int c) {
   return std::make_pair(n, useful > 0 ? area / useful : 1.0);
 }
 
-// Default configuration when the autotuner has not run: the largest tile that gives every compute
-// unit two tiles with little padding.
+// Default configuration of the reduced-precision kernels when the autotuner has not run: the largest
+// tile that gives every compute unit two tiles with little padding.
 static int default_config(const tamm_plan* p) {
   int best = 0;
   double best_score = -1;
   for (int c = 0; c < cfg_count(p->prec); ++c) {
     auto tw = tiles_for(p, c);
     const TileCfg f = cfg_get(p->prec, c);
-    if ((p->prec == TAMM_PREC_F64 && f.kt != 16) || f.threads != 256 || f.mt > 128 || f.nt > 128) continue;
+    if (f.threads != 256 || f.mt > 128 || f.nt > 128) continue;
     double score = (double)f.mt * f.nt / tw.second;
     if (tw.first < 512) score *= (double)tw.first / 512.0;
     if (score > best_score) {
@@ -563,6 +613,158 @@ static int default_config(const tamm_plan* p) {
     }
   }
   return best;
+}
+
+// K splits of a block's tiles: in proportion to its summed K extent, the heaviest blocks' get
+// k_splits parts, lighter ones fewer (at least one), so that the parts cost about the same.
+static int block_splits(int k_splits, double kext, double max_kext) {
+  if (k_splits <= 1 || max_kext <= 0) return 1;
+  return (int)std::min<double>(k_splits, std::max(1.0, std::floor(k_splits * kext / max_kext + 0.5)));
+}
+
+// Estimated time in microseconds of a float64 contraction over blocks of these shapes: the larger of
+// the longest item and the items' sum over the resident workgroups plus part of an item for the
+// tail, at least the time of the unavoidable traffic.  An item takes, per chunk of summed
+// indices, its products at the configuration's rate or one memory round trip, whichever is longer;
+// per pair and per item a few dependent loads, and an epilogue that grows with the tile.  The constants
+// were fitted to 108 contractions (3 kF to 6 TF, tiles of 3 to 64) timed with every configuration and
+// 1 to 16 K splits: taking the configuration with the least estimate costs 4 % against the best one
+// of each on average (up to 20 %), the rule before it (largest tile, no padding, two tiles per
+// compute unit) 14 % (up to 63 %).
+constexpr double kRoundTrip16 = 0.60, kRoundTrip32 = 0.70, kRoundTripWave = 0.78;  // a chunk of 16, of 32, of a one-wave workgroup
+constexpr double kPair = 0.137, kItem = 3.84, kPer1024 = 0.63, kTail = 0.42, kGroupTail = 0.3;
+constexpr double kReduce = 5.6, kReduceBytes = 5.0e6;  // launch, bytes per microsecond
+
+static double item_us(const BlockShape& b, const TileCfg& f, double area, double parts) {
+  const double rate = f.rate * 1e-6 / ((double)f.resident * kComputeUnits);  // flop per microsecond of a resident workgroup
+  const double lat = f.threads == 64 ? kRoundTripWave : (f.kt == 32 ? kRoundTrip32 : kRoundTrip16);
+  const double chunks = (double)(f.kt == 32 ? b.chunks32 : b.chunks16);
+  return (chunks * std::max(2.0 * area * f.kt / rate, lat) + (double)b.pairs * kPair) / parts + kItem + kPer1024 * area / 1024.0;
+}
+
+// Tiles of at most tm x tn of the blocks of one shape: fn(area of a tile, how many).
+template <typename F>
+static void for_tiles(const BlockShape& b, const TileCfg& f, int64_t tm, int64_t tn, F&& fn) {
+  const int64_t nm = (b.mext + tm - 1) / tm, um = (b.mext + f.um - 1) / f.um;  // tiles and units of the rows
+  const int64_t nn = (b.next + tn - 1) / tn, un = (b.next + f.un - 1) / f.un;
+  for (int hm = 0; hm < 2; ++hm)  // tiles of um / nm units, and the um % nm tiles of one more
+    for (int hn = 0; hn < 2; ++hn) {
+      const double n = (double)((hm ? um % nm : nm - um % nm) * (hn ? un % nn : nn - un % nn) * b.count);
+      if (n > 0) fn((double)((um / nm + hm) * f.um) * (double)((un / nn + hn) * f.un), n);
+    }
+}
+
+static double estimate_us(const std::vector<BlockShape>& shapes, const TileCfg& f, int k_splits, double bytes) {
+  const double slots = (double)f.resident * kComputeUnits;
+  double max_kext = 0, total = 0, longest = 0, items = 0, partial = 0;
+  for (const BlockShape& b : shapes) max_kext = std::max(max_kext, b.kext);
+  for (const BlockShape& b : shapes) {
+    const int ns = block_splits(k_splits, b.kext, max_kext);
+    const double parts = (double)std::min<int64_t>(ns, std::max<int64_t>(1, b.pairs));  // a pair is never cut
+    for_tiles(b, f, f.mt, f.nt, [&](double area, double n) {
+      const double t = item_us(b, f, area, parts);
+      total += t * n * parts;
+      items += n * parts;
+      longest = std::max(longest, t);
+    });
+    if (ns > 1) partial += (double)(b.mext * b.next * b.count) * ns;
+  }
+  double t = items > slots ? std::max(longest, total / slots + kTail * longest) : longest;
+  t = std::max(t, bytes / (f.resident > 2 ? 4.8e6 : 3.8e6));  // what copies reach with many and with few workgroups in flight
+  return t + (partial > 0 ? kReduce + partial * 16.0 / kReduceBytes : 0.0);
+}
+
+// Groups run without K splits, so a member with few output elements and long sums (the hole-hole
+// intermediate) would hold a launch up with a handful of long items.  Its tiles are cut smaller: the
+// largest tile, halved along its longer side down to 32 or one unit, whose item takes at most `limit`
+// us.  (No more tiles than the 32 x 32 configuration has, which the workspace has room for.)
+static std::pair<int32_t, int32_t> group_tile(const BlockShape& b, const TileCfg& f, double limit) {
+  int32_t tm = f.mt, tn = f.nt;
+  while (item_us(b, f, (double)std::min<int64_t>(tm, b.mext) * (double)std::min<int64_t>(tn, b.next), 1.0) > limit) {
+    const int32_t um = std::max(f.um, 32), un = std::max(f.un, 32);
+    const bool rows = (tm > um && (tm >= tn || tn <= un));
+    if (!rows && tn <= un) break;
+    int32_t& side = rows ? tm : tn;
+    const int32_t unit = rows ? um : un;
+    side = std::max(unit, side / 2 / unit * unit);
+  }
+  return std::make_pair(tm, tn);
+}
+
+// The limit of group_tile for the members of one launch: the launch's time if evenly spread.  (Of
+// 0.4, 0.7 and 1 times that, 1 gave the best mean over 17 schedules and groups, and no cut tiles at
+// all left the hole-hole intermediate's launch 1.4 times as long at O=26, V=102.)
+static double group_limit_us(const std::vector<BlockShape>& shapes, const TileCfg& f) {
+  double total = 0;
+  for (const BlockShape& b : shapes)
+    for_tiles(b, f, f.mt, f.nt, [&](double area, double n) { total += item_us(b, f, area, 1.0) * n; });
+  return total / ((double)f.resident * kComputeUnits);
+}
+
+// Estimated time of a group's launch over blocks of these shapes (estimate_us with cut tiles).
+static double group_estimate_us(const std::vector<BlockShape>& shapes, const TileCfg& f, double bytes) {
+  const double slots = (double)f.resident * kComputeUnits, limit = group_limit_us(shapes, f);
+  double total = 0, longest = 0;
+  for (const BlockShape& b : shapes) {
+    const auto tile = group_tile(b, f, limit);
+    for_tiles(b, f, tile.first, tile.second, [&](double area, double n) {
+      const double t = item_us(b, f, area, 1.0);
+      total += t * n;
+      longest = std::max(longest, t);
+    });
+  }
+  return std::max(std::max(longest, total / slots + kGroupTail * longest), bytes / (f.resident > 2 ? 4.8e6 : 3.8e6));
+}
+
+// Default configuration and K splits of a float64 plan: the least estimate; more splits only where
+// they are estimated to gain 3 %, and 8 % above a millisecond, where the queues have filled the tail
+// that splits would (ladder and its gradients at O=32, V=160: 3.1 ms in one part, 3.4 in four).  The partial tiles take at most an eighth of the tensors' bytes or 64 MiB.
+static std::pair<int, int> default_f64(const tamm_plan* p, int config, int k_splits) {
+  const double bytes = p->stats.algorithmic_bytes, budget = std::max(bytes / 8, (double)(64 << 20));
+  double best = 1e300, max_kext = 0;
+  std::pair<int, int> pick(std::max(config, 0), std::max(k_splits, 1));
+  for (const BlockShape& b : p->shapes) max_kext = std::max(max_kext, b.kext);
+  for (int ks : {1, 2, 4, 8, 16}) {
+    if (k_splits > 0 && ks > 1) break;
+    const int splits = k_splits > 0 ? k_splits : ks;
+    double least = 1e300;
+    int at = -1;
+    for (int c = 0; c < f64_config_count(); ++c) {
+      if (config >= 0 ? c != config : f64_config_canonical(c) != c) continue;
+      const TileCfg f = cfg_get(p->prec, c);
+      double need = 0;
+      for (const BlockShape& b : p->shapes) {
+        const int ns = block_splits(splits, b.kext, max_kext);
+        if (ns > 1) need += 8.0 * f.mt * f.nt * ns * (double)(((b.mext + f.mt - 1) / f.mt) * ((b.next + f.nt - 1) / f.nt) * b.count);
+      }
+      if (k_splits <= 0 && need > budget) continue;
+      const double t = estimate_us(p->shapes, f, splits, bytes);
+      if (t < least) {
+        least = t;
+        at = c;
+      }
+    }
+    if (at >= 0 && least < (best > 1000.0 ? 0.92 : 0.97) * best) {
+      best = least;
+      pick = std::make_pair(at, splits);
+    }
+  }
+  return pick;
+}
+
+// Extents of the tiles that cover `ext` rows (or columns): as many as whole tiles of `tile` would
+// take, of even sizes in whole `unit`s (16 rows for every wave along the dimension, the step in
+// which the float64 kernels' tile bodies come), the last one ending with the block.  A sliver of a
+// tile left at the end of a block would cost the loads, barriers and epilogue of a whole one.
+static void cut_extent(int32_t ext, int32_t tile, int32_t unit, std::vector<int32_t>& out) {
+  out.clear();
+  const int32_t n = (ext + tile - 1) / tile, units = (ext + unit - 1) / unit;
+  int32_t at = 0;
+  for (int32_t i = 0; i < n; ++i) {
+    const int32_t end = std::min(ext, (int32_t)((int64_t)units * (i + 1) / n) * unit);
+    out.push_back(end - at);
+    at = end;
+  }
 }
 
 // Launch order of the work items for the chip's eight accelerator dies (XCDs), each with its own
@@ -593,6 +795,33 @@ static void xcd_order(std::vector<WorkItem>& work, int chunk) {
   work.swap(out);
 }
 
+// The same chunks as the queues of a persistent launch: chunk c of the longest-first list goes to
+// queue c % 8, each queue's chunks in list order.  A workgroup takes its next item when it has ended
+// the last, so unequal items leave no slot empty until the queues run dry; the dispatcher, handing
+// out one workgroup per item in a fixed rotation, kept 76-92 % of the slots busy (ladder at O=40,
+// V=200, K splits 4 and 1).
+static void queue_order(std::vector<WorkItem>& work, size_t first, int chunk, int32_t* begin) {
+  const size_t n = work.size() - first, step = std::max(1, chunk);
+  std::vector<WorkItem> out;
+  out.reserve(n);
+  for (int x = 0; x < kQueues; ++x) {
+    begin[x] = (int32_t)out.size();
+    for (size_t c = x * step; c < n; c += kQueues * step)
+      for (size_t i = c; i < std::min(n, c + step); ++i) out.push_back(work[first + i]);
+  }
+  begin[kQueues] = (int32_t)out.size();
+  std::copy(out.begin(), out.end(), work.begin() + first);
+}
+
+// Whether a persistent launch pays: more items than resident workgroups, and items long enough.
+// Taking an item costs two barriers and an atomic that goes past the dies' L2s, about 2 us; items of
+// a few microseconds lost a factor of two and more by it (the T1 terms at O=40, V=200: 0.10 -> 0.24
+// and 0.28 -> 0.43 ms), items of 190 us and more gained (hh 0.62 -> 0.57, ring 2.76 -> 2.53 ms).
+static bool queue_pays(double flops, size_t items, const TileCfg& f) {
+  const size_t slots = (size_t)f.resident * kComputeUnits;
+  return items > slots && flops / (double)items / (f.rate / (double)slots) >= 40e-6;
+}
+
 static int xcd_chunk() {
   static const int v = [] {
     const char* e = getenv("TAMM_XCD_CHUNK");
@@ -601,14 +830,76 @@ static int xcd_chunk() {
   return v;
 }
 
+// Workspace layout of a plan: static tables and pair lists, work list, reduce list, queue counters,
+// partial tiles, and for the split-bfloat16 precisions the split operands.
+static void layout_workspace(tamm_plan* p, const TileCfg& f, size_t items, size_t reduces, size_t partials, bool queued) {
+  p->lay = make_layout(p, 0);
+  size_t off = p->lay.end;
+  p->off_work = off;
+  off = align256(off + items * sizeof(WorkItem));
+  p->off_reduce = off;
+  off = align256(off + reduces * sizeof(ReduceItem));
+  p->off_queue = off;
+  if (queued) off = align256(off + kQueueSlots * kQueues * sizeof(int32_t));
+  p->off_partial = off;
+  if (partials > 0) off = align256(off + partials * f.mt * f.nt * sizeof(double));
+  if (p->prec == TAMM_PREC_BF16X3 || p->prec == TAMM_PREC_BF16X4_ALIGNED) {
+    p->off_prepA = off;
+    off = align256(off + p->prepA.size() * sizeof(PrepBlock));
+    p->off_prepB = off;
+    off = align256(off + p->prepB.size() * sizeof(PrepBlock));
+    p->off_xA = off;
+    off = align256(off + (size_t)p->A->numel * sizeof(uint64_t));
+    p->off_xB = off;
+    off = align256(off + (size_t)p->B->numel * sizeof(uint64_t));
+  }
+  p->ws_size = std::max<size_t>(off, 256);
+}
+
+// The largest workspace of any configuration with 1, 2, .. max_splits K splits, without building
+// their work lists.
+size_t tamm::plan_candidate_workspace(const tamm_plan* p, int max_splits) {
+  tamm_plan size_only;
+  size_only.A = p->A;
+  size_only.B = p->B;
+  size_only.prec = p->prec;
+  size_only.pool.resize(p->pool.size());
+  size_only.blocks.resize(p->blocks.size());
+  size_only.n_kt = p->n_kt;
+  size_only.prepA.resize(p->prepA.size());
+  size_only.prepB.resize(p->prepB.size());
+  double max_kext = 0;
+  for (const BlockShape& b : p->shapes) max_kext = std::max(max_kext, b.kext);
+  size_t most = 0;
+  for (int c = 0; c < cfg_count(p->prec); ++c) {
+    if (p->prec == TAMM_PREC_F64 && f64_config_canonical(c) != c) continue;
+    const TileCfg f = cfg_get(p->prec, c);
+    for (int ks = 1; ks <= max_splits; ks *= 2) {
+      size_t items = 0, reduces = 0, partials = 0;
+      for (const BlockShape& b : p->shapes) {
+        const int ns = block_splits(ks, b.kext, max_kext);
+        const size_t tiles = (size_t)(((b.mext + f.mt - 1) / f.mt) * ((b.next + f.nt - 1) / f.nt) * b.count);
+        items += tiles * ns;
+        if (ns > 1) reduces += tiles;
+        if (ns > 1) partials += tiles * ns;
+      }
+      if (partials > (size_t)INT32_MAX / 2 || items > (size_t)INT32_MAX / 2) continue;  // configure_work refuses it
+      layout_workspace(&size_only, f, items, reduces, partials, p->prec == TAMM_PREC_F64);
+      most = std::max(most, size_only.ws_size);
+    }
+  }
+  return most;
+}
+
 // Work decomposition for one kernel configuration: macro-tiles of every stored output block,
 // heaviest first (longest-processing-time order), with the K splits of a tile adjacent, then laid
 // out for the dies (xcd_order).
 static int configure_work(tamm_plan* p, int config, int k_splits) {
   const int ncfg = cfg_count(p->prec);
   const int64_t nob = (int64_t)p->blocks.size();
-  if (config < 0) config = default_config(p);
   if (config >= ncfg) return fail(TAMM_ERR_ARG, "kernel configuration %d does not exist (%d available)", config, ncfg);
+  if (p->prec == TAMM_PREC_F64 && (config < 0 || k_splits <= 0)) std::tie(config, k_splits) = default_f64(p, config, k_splits);
+  if (config < 0) config = default_config(p);
   const TileCfg f = cfg_get(p->prec, config);
   const int64_t ntiles = tiles_for(p, config).first;
   if (k_splits <= 0) {
@@ -625,18 +916,25 @@ static int configure_work(tamm_plan* p, int config, int k_splits) {
   if (k_splits > 64) return fail(TAMM_ERR_ARG, "k_splits must be in [1, 64]");
   struct Tile {
     double cost;
-    int32_t ob, m0, n0;
+    int32_t ob, m0, n0, rows, cols;
   };
   std::vector<Tile> tiles;
   tiles.reserve(ntiles);
+  std::vector<int32_t> cm, cn;
   for (int64_t b = 0; b < nob; ++b) {
     const auto& d = p->blocks[b];
-    for (int32_t m0 = 0; m0 < d.mext; m0 += f.mt)
-      for (int32_t n0 = 0; n0 < d.next; n0 += f.nt)
-        tiles.push_back(Tile{p->block_cost[b] * std::min(f.mt, d.mext - m0) * std::min(f.nt, d.next - n0), (int32_t)b, m0, n0});
+    cut_extent(d.mext, f.mt, f.um, cm);
+    cut_extent(d.next, f.nt, f.un, cn);
+    int32_t m0 = 0;
+    for (int32_t rows : cm) {
+      int32_t n0 = 0;
+      for (int32_t cols : cn) {
+        tiles.push_back(Tile{p->block_cost[b] * rows * cols, (int32_t)b, m0, n0, rows, cols});
+        n0 += cols;
+      }
+      m0 += rows;
+    }
   }
-  // K splits per tile in proportion to its block's summed K extent: tiles of the heaviest blocks
-  // get k_splits parts, lighter ones fewer (at least one), so that the parts cost about the same
   double max_cost = 0;
   for (const Tile& t : tiles) max_cost = std::max(max_cost, p->block_cost[t.ob]);
   struct Part {
@@ -647,13 +945,11 @@ static int configure_work(tamm_plan* p, int config, int k_splits) {
   p->reduce.clear();
   int64_t slots = 0;
   for (const Tile& t : tiles) {
-    int ns = 1;
-    if (k_splits > 1 && max_cost > 0)
-      ns = (int)std::min<double>(k_splits, std::max(1.0, std::floor(k_splits * p->block_cost[t.ob] / max_cost + 0.5)));
+    const int ns = block_splits(k_splits, p->block_cost[t.ob], max_cost);
     for (int s = 0; s < ns; ++s)
-      parts.push_back(Part{t.cost / ns, WorkItem{0, t.ob, t.m0, t.n0, encode_split(s, ns), (int32_t)slots}});
+      parts.push_back(Part{t.cost / ns, WorkItem{0, t.ob, t.m0, t.n0, item_shape(s, ns, t.rows, t.cols), (int32_t)slots}});
     if (ns > 1) {
-      p->reduce.push_back(ReduceItem{0, t.ob, t.m0, t.n0, (int32_t)slots, ns});
+      p->reduce.push_back(ReduceItem{0, t.ob, t.m0, t.n0, (int32_t)slots, item_shape(0, ns, t.rows, t.cols)});
       slots += ns;
     }
     if (slots > INT32_MAX / 2) return fail(TAMM_ERR_UNSUPPORTED, "too many partial tiles");
@@ -678,7 +974,10 @@ static int configure_work(tamm_plan* p, int config, int k_splits) {
   p->work.clear();
   for (const Part& q : parts) p->work.push_back(q.w);
   if (p->work.size() > (size_t)INT32_MAX / 2) return fail(TAMM_ERR_UNSUPPORTED, "too many work items");
-  xcd_order(p->work, p->xcd_chunk >= 0 ? p->xcd_chunk : xcd_chunk());
+  const int chunk = p->xcd_chunk >= 0 ? p->xcd_chunk : xcd_chunk();
+  p->queued = p->prec == TAMM_PREC_F64 && !p->no_queue && queue_pays(p->stats.useful_flops, p->work.size(), f);
+  if (p->queued) queue_order(p->work, 0, chunk, p->queue_begin);
+  else xcd_order(p->work, chunk);
   p->config = config;
   p->k_splits = k_splits;
   p->stats.work_items = (int64_t)p->work.size();
@@ -687,25 +986,7 @@ static int configure_work(tamm_plan* p, int config, int k_splits) {
   p->stats.xcd_chunk = p->xcd_chunk >= 0 ? p->xcd_chunk : xcd_chunk();
   p->stats.tile_order = p->tile_order;
   p->stats.gather_layout = gather_layout(p);
-  p->lay = make_layout(p, 0);
-  size_t off = p->lay.end;
-  p->off_work = off;
-  off = align256(off + p->work.size() * sizeof(WorkItem));
-  p->off_reduce = off;
-  off = align256(off + p->reduce.size() * sizeof(ReduceItem));
-  p->off_partial = off;
-  if (slots > 0) off = align256(off + (size_t)slots * f.mt * f.nt * sizeof(double));
-  if (p->prec == TAMM_PREC_BF16X3 || p->prec == TAMM_PREC_BF16X4_ALIGNED) {
-    p->off_prepA = off;
-    off = align256(off + p->prepA.size() * sizeof(PrepBlock));
-    p->off_prepB = off;
-    off = align256(off + p->prepB.size() * sizeof(PrepBlock));
-    p->off_xA = off;
-    off = align256(off + (size_t)p->A->numel * sizeof(uint64_t));
-    p->off_xB = off;
-    off = align256(off + (size_t)p->B->numel * sizeof(uint64_t));
-  }
-  p->ws_size = std::max<size_t>(off, 256);
+  layout_workspace(p, f, p->work.size(), p->reduce.size(), (size_t)slots, p->queued);
   p->ws_bound = false;
   p->screened = false;
   p->executed = false;
@@ -822,17 +1103,36 @@ extern "C" int tamm_plan_screen(tamm_plan* p, void* stream) {
   return ok();
 }
 
+// Workgroups of a persistent launch: every resident slot of the device (compute units x resident
+// workgroups of the configuration), at most one per item.
+static int persistent_grid(int config, int layout, int n_work) {
+  int dev = 0, cus = kComputeUnits;
+  if (hipGetDevice(&dev) == hipSuccess) {
+    int v = 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
+  }
+  return std::max(1, std::min<int>(f64_occupancy(config, layout) * cus, n_work));
+}
+
 static int contract_launch(tamm_plan* p, double alpha, double beta, hipStream_t s) {
   ContractParams cp{};
   cp.single = problem_desc(p, p->ws, p->lay, p->k_splits > 1 ? (double*)(p->ws + p->off_partial) : nullptr, p->k_splits,
                            alpha, beta);
   cp.probs = nullptr;
   cp.work = (const WorkItem*)(p->ws + p->off_work);
-  cp.next_item = nullptr;
   cp.n_work = (int32_t)p->work.size();
   const int layout = gather_layout(p);
   if (p->prec == TAMM_PREC_F64) {
-    HIP_TRY(launch_contract_f64(p->config, layout, cp, 0, s));
+    int grid = 0;
+    if (p->queued) {
+      // launches of one plan on different streams take counter sets of their own
+      cp.queue_next = (int32_t*)(p->ws + p->off_queue) + p->queue_slot * kQueues;
+      p->queue_slot = (p->queue_slot + 1) % kQueueSlots;
+      std::copy(p->queue_begin, p->queue_begin + kQueues + 1, cp.queue_begin);
+      grid = persistent_grid(p->config, layout, cp.n_work);
+      HIP_TRY(launch_clear_queues(cp.queue_next, s));
+    }
+    HIP_TRY(launch_contract_f64(p->config, layout, cp, grid, s));
   } else {
     if (p->prec != TAMM_PREC_F32) {
       // operand split into packed bfloat16 slices, then the contraction reads the split copies
@@ -1030,6 +1330,24 @@ extern "C" int tamm_contract_workspace_size(tamm_tensor* out, const char* out_lb
   return ok();
 }
 
+// Workspace of the cached plan for a caller with `limit` bytes: without the queue counters when
+// they alone would put it past the limit.
+int tamm::contract_workspace_within(tamm_tensor* out, const char* out_lbl, const tamm_tensor* lhs, const char* lhs_lbl,
+                                    const tamm_tensor* rhs, const char* rhs_lbl, int32_t precision, size_t limit, size_t* bytes) {
+  ContractCache& c = contract_cache();
+  std::lock_guard<std::mutex> lock(c.mu);
+  tamm_plan* p = nullptr;
+  int rc = cached_plan(c, out, out_lbl, lhs, lhs_lbl, rhs, rhs_lbl, precision, &p);
+  if (rc != TAMM_OK) return rc;
+  if (p->ws_size > limit && p->queued) {
+    p->no_queue = true;
+    rc = configure_work(p, p->config, p->k_splits);
+    if (rc != TAMM_OK) return rc;
+  }
+  *bytes = p->ws_size;
+  return TAMM_OK;
+}
+
 extern "C" int tamm_contract(tamm_tensor* out, const char* out_lbl, const tamm_tensor* lhs, const char* lhs_lbl,
                              const tamm_tensor* rhs, const char* rhs_lbl, int32_t precision, double alpha, double beta,
                              void* workspace, size_t bytes, void* stream) {
@@ -1137,14 +1455,7 @@ void cache_store(const char* path, uint64_t sig, const char* kind, const CacheEn
 
 extern "C" int tamm_plan_autotune_workspace_size(const tamm_plan* p, size_t* bytes) {
   if (!p || !bytes) return fail(TAMM_ERR_ARG, "null argument");
-  tamm_plan tmp = *p;
-  size_t mx = 0;
-  for (int c = 0; c < cfg_count(p->prec); ++c)
-    for (int ks : {1, 2, 4, 8}) {
-      if (configure_work(&tmp, c, ks) != TAMM_OK) continue;
-      mx = std::max(mx, tmp.ws_size);
-    }
-  *bytes = mx;
+  *bytes = plan_candidate_workspace(p, 8);
   return ok();
 }
 
@@ -1184,6 +1495,7 @@ extern "C" int tamm_plan_autotune(tamm_plan* p, void* workspace, size_t bytes, v
     const int64_t ntiles_max = tiles_for(p, 0).first;
     std::vector<CacheEntry> ranked;  // every (configuration, K splits) at the current launch order
     for (int c = 0; c < cfg_count(p->prec) && rc == TAMM_OK; ++c) {
+      if (p->prec == TAMM_PREC_F64 && f64_config_canonical(c) != c) continue;  // another id of a kernel already timed
       const int64_t nt = tiles_for(p, c).first;
       for (int ks : {1, 2, 4, 8}) {
         if (ks > 1 && nt * ks > 4 * std::max<int64_t>(ntiles_max, 2048)) continue;
@@ -1269,6 +1581,7 @@ extern "C" int tamm_plan_autotune(tamm_plan* p, void* workspace, size_t bytes, v
 // the same output tiles (a fused node, built by the scheduler): their pair lists are screened
 // into one list per output block and one output tile's K loop runs over all of them.
 // ---------------------------------------------------------------------------------------------
+constexpr int kGroupChunk = 8;  // items per die chunk of a group's queues
 struct tamm_group {
   std::vector<std::vector<tamm_plan*>> nodes;  // member plans of each node
   std::vector<tamm_plan*> plans;               // every member plan, node by node
@@ -1283,6 +1596,8 @@ struct tamm_group {
   std::vector<int32_t> sitem_prob, sitem_block;  // screening items: first segment of the node, output block
   std::vector<WorkItem> work;       // grouped by gather layout class, each class longest first (prob = node)
   size_t work_capacity = 0;         // work items of the largest mix of per-class configurations
+  int32_t queue_begin[kLayouts][kQueues + 1] = {};  // each class's queues, relative to its work range
+  bool queued[kLayouts] = {};            // a persistent launch pays (queue_pays)
   int32_t cls_begin[kLayouts + 1] = {};  // work range of gather layout c: [cls_begin[c], cls_begin[c+1])
   int cfg[kLayouts] = {};   // kernel configuration of each layout class (its tile shape)
   int grid[kLayouts] = {};  // persistent grid of each layout class (0: automatic)
@@ -1325,25 +1640,46 @@ static double node_block_cost(const tamm_group* g, size_t q, size_t b) {
   return c;
 }
 
-// Default configuration of a set of nodes: the one with the least padding, ties to the larger
-// tile.
+// Shape of output block b of a node: of its plan, or of the plans that share its output tiles, their
+// pairs one after another.
+static BlockShape node_block_shape(const tamm_group* g, size_t q, size_t b) {
+  BlockShape sh = g->nodes[q][0]->block_shapes[b];
+  for (size_t i = 1; i < g->nodes[q].size(); ++i) {
+    const BlockShape& o = g->nodes[q][i]->block_shapes[b];
+    sh.pairs += o.pairs;
+    sh.chunks16 += o.chunks16;
+    sh.chunks32 += o.chunks32;
+    sh.kext += o.kext;
+  }
+  return sh;
+}
+
+// The distinct block shapes of the nodes of one layout class, and the bytes of their tensors.
+static std::vector<BlockShape> class_shapes(const tamm_group* g, int layout, double* bytes) {
+  std::vector<BlockShape> shapes;
+  *bytes = 0;
+  for (size_t q = 0; q < g->nodes.size(); ++q) {
+    if (node_layout(g, q) != layout) continue;
+    if (g->nodes[q].size() == 1) shapes.insert(shapes.end(), g->nodes[q][0]->shapes.begin(), g->nodes[q][0]->shapes.end());
+    else
+      for (size_t b = 0; b < g->nodes[q][0]->blocks.size(); ++b) shapes.push_back(node_block_shape(g, q, b));
+    for (const tamm_plan* p : g->nodes[q]) *bytes += p->stats.algorithmic_bytes;
+  }
+  merge_shapes(shapes);
+  return shapes;
+}
+
+// Default configuration of the nodes of one layout class: the least estimated time of its launch.
 static int group_default_config(const tamm_group* g, int layout) {
+  double bytes = 0;
+  const std::vector<BlockShape> shapes = class_shapes(g, layout, &bytes);
   int config = 0;
-  double best = 1e30;
+  double best = 1e300;
   for (int c = 0; c < f64_config_count(); ++c) {
-    const F64Config& f = f64_config(c);
-    if (f.kt != 16 || f.wgm * f.wgn != 4 || f.mt > 128 || f.nt > 128) continue;
-    double area = 0, useful = 0;
-    for (size_t q = 0; q < g->nodes.size(); ++q) {
-      if (layout >= 0 && node_layout(g, q) != layout) continue;
-      for (const auto& b : g->nodes[q][0]->blocks) {
-        area += (double)((b.mext + f.mt - 1) / f.mt) * f.mt * ((b.next + f.nt - 1) / f.nt) * f.nt;
-        useful += (double)b.mext * b.next;
-      }
-    }
-    const double score = (useful > 0 ? area / useful : 1.0) - 1e-6 * f.mt * f.nt;
-    if (score < best) {
-      best = score;
+    if (f64_config_canonical(c) != c) continue;
+    const double t = group_estimate_us(shapes, cfg_get(TAMM_PREC_F64, c), bytes);
+    if (t < best) {
+      best = t;
       config = c;
     }
   }
@@ -1364,8 +1700,11 @@ static int group_configure_classes(tamm_group* g, const int* cfgs) {
   };
   g->work.clear();
   for (int c = 0; c < kLayouts; ++c) {
-    const F64Config& f = f64_config(g->cfg[c]);
     std::vector<Tile> tiles;
+    std::vector<int32_t> cm, cn;
+    const TileCfg tc = cfg_get(TAMM_PREC_F64, g->cfg[c]);
+    double bytes = 0;
+    const double limit = group_limit_us(class_shapes(g, c, &bytes), tc);
     for (size_t q = 0; q < g->nodes.size(); ++q) {
       if (node_layout(g, q) != c) continue;
       const tamm_plan* p = g->nodes[q][0];
@@ -1373,15 +1712,27 @@ static int group_configure_classes(tamm_group* g, const int* cfgs) {
       for (size_t b = 0; b < p->blocks.size(); ++b) {
         const auto& d = p->blocks[b];
         const double bc = node_block_cost(g, q, b);
-        for (int32_t m0 = 0; m0 < d.mext; m0 += f.mt)
-          for (int32_t n0 = 0; n0 < d.next; n0 += f.nt)
-            tiles.push_back(Tile{bc * std::min(f.mt, d.mext - m0) * std::min(f.nt, d.next - n0),
-                                 WorkItem{(int32_t)q, (int32_t)b, m0, n0, 0, t++}});
+        const auto tile = group_tile(node_block_shape(g, q, b), tc, limit);
+        cut_extent(d.mext, tile.first, tc.um, cm);
+        cut_extent(d.next, tile.second, tc.un, cn);
+        int32_t m0 = 0;
+        for (int32_t rows : cm) {
+          int32_t n0 = 0;
+          for (int32_t cols : cn) {
+            tiles.push_back(Tile{bc * rows * cols, WorkItem{(int32_t)q, (int32_t)b, m0, n0, item_shape(0, 1, rows, cols), t++}});
+            n0 += cols;
+          }
+          m0 += rows;
+        }
       }
     }
     std::stable_sort(tiles.begin(), tiles.end(), [](const Tile& x, const Tile& y) { return x.cost > y.cost; });
     g->cls_begin[c] = (int32_t)g->work.size();
     for (auto& t : tiles) g->work.push_back(t.w);
+    double flops = 0;
+    for (const Tile& t : tiles) flops += 2.0 * t.cost;
+    g->queued[c] = queue_pays(flops, tiles.size(), cfg_get(TAMM_PREC_F64, g->cfg[c]));
+    queue_order(g->work, g->cls_begin[c], kGroupChunk, g->queue_begin[c]);
   }
   g->cls_begin[kLayouts] = (int32_t)g->work.size();
   size_t off = 0;
@@ -1415,8 +1766,8 @@ static int group_configure_classes(tamm_group* g, const int* cfgs) {
   // room for any mix of per-class configurations, so the autotuner's choice always fits the
   // workspace sized for the candidates
   off = align256(off + std::max(g->work.size(), g->work_capacity) * sizeof(WorkItem));
-  g->off_counter = off;  // one work counter per gather layout
-  off = align256(off + kLayouts * sizeof(int32_t));
+  g->off_counter = off;  // the queue counters of every gather layout
+  off = align256(off + kLayouts * kQueues * sizeof(int32_t));
   g->ws_size = off;
   g->bound = false;
   group_drop_graph(g);
@@ -1488,6 +1839,7 @@ int group_create_nodes(const std::vector<std::vector<tamm_plan*>>& nodes, tamm_g
   for (int c = 0; c < kLayouts; ++c) {
     size_t most = 0;
     for (int k = 0; k < f64_config_count(); ++k) {
+      if (f64_config_canonical(k) != k) continue;
       const F64Config& f = f64_config(k);
       size_t n = 0;
       for (size_t q = 0; q < g->nodes.size(); ++q)
@@ -1607,16 +1959,10 @@ extern "C" int tamm_group_set_config(tamm_group* g, int32_t config, int32_t grid
   return ok();
 }
 
-// Persistent grid of one layout class: the tuned size, else every resident slot of the device
-// (compute units x resident workgroups of the configuration).
+// Persistent grid of one layout class: the tuned size, else every resident slot of the device.
 static int group_grid(const tamm_group* g, int layout, int n_work) {
   if (g->grid[layout] > 0) return std::max(1, std::min<int>(g->grid[layout], n_work));
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) == hipSuccess) {
-    int v = 0;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
-  }
-  return std::max(1, std::min<int>(f64_occupancy(g->cfg[layout], layout) * cus, n_work));
+  return persistent_grid(g->cfg[layout], layout, n_work);
 }
 
 // The persistent contraction launch of one layout class (counter reset first); nothing for an
@@ -1624,13 +1970,16 @@ static int group_grid(const tamm_group* g, int layout, int n_work) {
 static int group_enqueue_class(tamm_group* g, int c, hipStream_t s) {
   const int n = g->cls_begin[c + 1] - g->cls_begin[c];
   if (n <= 0) return TAMM_OK;
-  const int grid = group_grid(g, c, n);
-  int32_t* counter = (int32_t*)(g->ws + g->off_counter) + c;
-  HIP_TRY(launch_set_counter(counter, grid, s));
   ContractParams cp{};
+  int grid = 0;
+  if (g->grid[c] > 0 || g->queued[c]) {
+    grid = group_grid(g, c, n);
+    cp.queue_next = (int32_t*)(g->ws + g->off_counter) + c * kQueues;
+    std::copy(g->queue_begin[c], g->queue_begin[c] + kQueues + 1, cp.queue_begin);
+    HIP_TRY(launch_clear_queues(cp.queue_next, s));
+  }
   cp.probs = (const ProblemDesc*)(g->ws + g->off_pdesc);
   cp.work = (const WorkItem*)(g->ws + g->off_work) + g->cls_begin[c];
-  cp.next_item = counter;
   cp.n_work = n;
   HIP_TRY(launch_contract_f64(g->cfg[c], c, cp, grid, s));
   return TAMM_OK;
@@ -1827,6 +2176,7 @@ int group_autotune(tamm_group* g, hipStream_t s, const char* cache_path, int32_t
     int cus = 256, dev = 0;
     if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     for (int k = 0; k < f64_config_count() && rc == TAMM_OK; ++k) {
+      if (f64_config_canonical(k) != k) continue;  // another id of a kernel already timed
       for (int mult : {0, 1, 2, 4}) {  // 0: every resident slot (occupancy-sized grid)
         if (rc != TAMM_OK) break;  // a failed launch ends the search with its error
         if ((rc = group_configure(g, k)) != TAMM_OK) break;
@@ -1868,16 +2218,9 @@ int group_autotune(tamm_group* g, hipStream_t s, const char* cache_path, int32_t
 
 size_t group_workspace_size(const tamm_group* g) { return g->ws_size; }
 
-// The largest workspace any configuration of the group needs (the autotuner's candidates).
-size_t group_autotune_workspace_size(tamm_group* g) {
-  size_t best = g->ws_size;
-  int cfgs[kLayouts];
-  for (int c = 0; c < kLayouts; ++c) cfgs[c] = g->cfg[c];
-  for (int k = 0; k < f64_config_count(); ++k)
-    if (group_configure(g, k) == TAMM_OK) best = std::max(best, g->ws_size);
-  (void)group_configure_classes(g, cfgs);
-  return best;
-}
+// The largest workspace any configuration of the group needs: its layout reserves room for the work
+// lists of any mix of them.
+size_t group_autotune_workspace_size(tamm_group* g) { return g->ws_size; }
 
 int group_bind_ws(tamm_group* g, void* ws, size_t bytes) { return group_bind(g, ws, bytes); }
 
