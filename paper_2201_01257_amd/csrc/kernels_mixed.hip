@@ -453,27 +453,27 @@ struct PlaneGather {
     kext = d.kext;
   }
   __device__ void load_tables(const PairDesc&, const int32_t*, int kb) { kbase = kb; }
-  __device__ void load_data() {
-    const uint32_t a_bytes = (uint32_t)mext * (uint32_t)kext * 2u, b_bytes = (uint32_t)next * (uint32_t)kext * 2u;
-#pragma unroll
-    for (int sl = 0; sl < NS; ++sl) {
-      const __amdgpu_buffer_rsrc_t ar = block_rsrc(a_base + sl * a_plane, a_bytes);
-      const __amdgpu_buffer_rsrc_t br = block_rsrc(b_base + sl * b_plane, b_bytes);
-#pragma unroll
-      for (int j = 0; j < AJ; ++j) {
-        const int p = tid + j * NTHR, r = m0 + p / KG, k = kbase + 8 * (p % KG);
-        if (!a_live(p)) continue;
-        const uint32_t off = (r < mext && k < kext) ? (uint32_t)(r * kext + k) * 2u : kPast;
-        ra[sl][j] = __builtin_bit_cast(u4_t, __builtin_amdgcn_raw_buffer_load_b128(ar, (int)off, 0, 0));
-      }
-#pragma unroll
-      for (int j = 0; j < BJ; ++j) {
-        const int p = tid + j * NTHR, r = n0 + p / KG, k = kbase + 8 * (p % KG);
-        if (!b_live(p)) continue;
-        const uint32_t off = (r < next && k < kext) ? (uint32_t)(r * kext + k) * 2u : kPast;
-        rb[sl][j] = __builtin_bit_cast(u4_t, __builtin_amdgcn_raw_buffer_load_b128(br, (int)off, 0, 0));
-      }
+  // load y of the chunk: slice y / (AJ + BJ), A's loads before B's
+  static constexpr int kLoads = NS * (AJ + BJ);
+  __device__ void load_one(int y) {
+    const int sl = y / (AJ + BJ), j = y % (AJ + BJ);
+    if (j < AJ) {
+      const int p = tid + j * NTHR, r = m0 + p / KG, k = kbase + 8 * (p % KG);
+      if (!a_live(p)) return;
+      const __amdgpu_buffer_rsrc_t ar = block_rsrc(a_base + sl * a_plane, (uint32_t)mext * (uint32_t)kext * 2u);
+      const uint32_t off = (r < mext && k < kext) ? (uint32_t)(r * kext + k) * 2u : kPast;
+      ra[sl][j] = __builtin_bit_cast(u4_t, __builtin_amdgcn_raw_buffer_load_b128(ar, (int)off, 0, 0));
+    } else {
+      const int jb = j - AJ, p = tid + jb * NTHR, r = n0 + p / KG, k = kbase + 8 * (p % KG);
+      if (!b_live(p)) return;
+      const __amdgpu_buffer_rsrc_t br = block_rsrc(b_base + sl * b_plane, (uint32_t)next * (uint32_t)kext * 2u);
+      const uint32_t off = (r < next && k < kext) ? (uint32_t)(r * kext + k) * 2u : kPast;
+      rb[sl][jb] = __builtin_bit_cast(u4_t, __builtin_amdgcn_raw_buffer_load_b128(br, (int)off, 0, 0));
     }
+  }
+  __device__ void load_data() {
+#pragma unroll
+    for (int y = 0; y < kLoads; ++y) load_one(y);
   }
   // LDS position (row, first k) of load j
   __device__ int lds_row(int j) const { return (tid + j * NTHR) / KG; }
@@ -538,37 +538,140 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_contract_bf16s(ContractParam
       lead[i][j] = (f4_t){0.f, 0.f, 0.f, 0.f};
       rest[i][j] = (f4_t){0.f, 0.f, 0.f, 0.f};
     }
-  if (pb < pe) {
-    auto store = [&](int b) {
-      if constexpr (PLANES) {  // 8 slices of one plane per 16-byte store
+  auto flush_window = [&]() {  // end of a promotion window or of a pair: float32 sums into float64
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
-          for (int j = 0; j < G::AJ; ++j) {
-            if (!G::a_live(tid + j * NTHR)) continue;
-            *reinterpret_cast<u4_t*>(&As[b][s * MT * LD + 8 * lds_unit<MT>(g.lds_row(j), g.lds_k(j) / 8)]) = g.ra[s][j];
-          }
+      for (int j = 0; j < FN; ++j)
 #pragma unroll
-          for (int j = 0; j < G::BJ; ++j) {
-            if (!G::b_live(tid + j * NTHR)) continue;
-            *reinterpret_cast<u4_t*>(&Bs[b][s * NT * LD + 8 * lds_unit<NT>(g.lds_row(j), g.lds_k(j) / 8)]) = g.rb[s][j];
-          }
+        for (int r = 0; r < 4; ++r) {
+          acc[i][j][r] += (double)lead[i][j][r] + (double)rest[i][j][r];
+          lead[i][j][r] = 0.f;
+          rest[i][j][r] = 0.f;
         }
-      } else {  // one packed element: its NS slices to NS planes
-        unsigned short* As16 = reinterpret_cast<unsigned short*>(As[b]);
-        unsigned short* Bs16 = reinterpret_cast<unsigned short*>(Bs[b]);
-#pragma unroll
-        for (int e = 0; e < G::AE; ++e) {
-          const int o = g.a_lds_row(e) * LD + g.a_lds_k(e);
-#pragma unroll
-          for (int s = 0; s < NS; ++s) As16[s * MT * LD + o] = (unsigned short)(g.ra[e] >> (16 * s));
+  };
+  if constexpr (PLANES) {
+    if (pb < pe) {
+      // products of one output fragment, in order: slice pairs (a, b) of the accumulators; product 0
+      // goes to the lead sum, the others to the residual's
+      constexpr int NP = ALIGNED ? 10 : 6;
+      constexpr int PA[10] = {0, 0, 1, 0, 2, 1, 0, 3, 1, 2}, PB[10] = {0, 1, 0, 2, 0, 1, 3, 0, 2, 1};
+      // The operand with more fragments per wave is streamed one fragment at a time (two register
+      // sets), the other stays in registers for the chunk: 64 + 32 registers of operands at most.
+      constexpr bool SA = FM > FN;                       // A streamed, else B
+      constexpr int FR = SA ? FN : FM, FS = SA ? FM : FN;
+      constexpr int NX = NP * FR;                        // products of one streamed fragment
+      constexpr int NL = G::kLoads, NSTAGE = NX * (FS - 1);  // products that the staging spreads over
+      static_assert(FS % 2 == 0, "the first and last streamed fragment use different register sets");
+      bf8_t res[NS][FR], str[2][NS];
+      auto fetch = [&](int b, bool a, int s, int f) {
+        return a ? *reinterpret_cast<const bf8_t*>(&As[b][s * MT * LD + a_frag[f]])
+                 : *reinterpret_cast<const bf8_t*>(&Bs[b][s * NT * LD + b_frag[f]]);
+      };
+      auto fetch_resident = [&](int b, auto s, auto f) { res[s()][f()] = fetch(b, !SA, s(), f()); };
+      auto fetch_streamed = [&](int b, auto s, auto f) { str[f() & 1][s()] = fetch(b, SA, s(), f()); };
+      // the last product that uses resident slice s
+      constexpr auto last_use = [](int s) {
+        constexpr int qa[10] = {0, 0, 1, 0, 2, 1, 0, 3, 1, 2}, qb[10] = {0, 1, 0, 2, 0, 1, 3, 0, 2, 1};
+        int at = -1;
+        for (int p = 0; p < NP; ++p)
+          if ((SA ? qb[p] : qa[p]) == s) at = p;
+        return at;
+      };
+      auto stage_one = [&](int b, auto y) {
+        constexpr int sl = y() / (G::AJ + G::BJ), j = y() % (G::AJ + G::BJ);
+        if constexpr (j < G::AJ) {
+          if (G::a_live(tid + j * NTHR))
+            *reinterpret_cast<u4_t*>(&As[b][sl * MT * LD + 8 * lds_unit<MT>(g.lds_row(j), g.lds_k(j) / 8)]) = g.ra[sl][j];
+        } else {
+          constexpr int jb = j - G::AJ;
+          if (G::b_live(tid + jb * NTHR))
+            *reinterpret_cast<u4_t*>(&Bs[b][sl * NT * LD + 8 * lds_unit<NT>(g.lds_row(jb), g.lds_k(jb) / 8)]) = g.rb[sl][jb];
         }
+        g.load_one(y());
+      };
+      ChunkWalk<KT, G, E> walk(g, pairs, pb, pe, pool, Ap, Bp, w, blk.mext, blk.next);
+      uint32_t flushes = 0;  // of the chunks fetched and not yet multiplied, the oldest in bit 0
+      int ahead = 0;
+      auto note = [&]() {
+        const int kend = walk.k + KT;
+        flushes |= (kend >= walk.d.kext || kend % kSplitWindow == 0 ? 1u : 0u) << ahead;
+        ++ahead;
+      };
+      auto next_chunk = [&]() {
+        const bool more = walk.next_tables();
+        if (more) note();
+        return more;
+      };
+      walk.setup();
+      g.load_tables(walk.d, pool, 0);
+      note();
+      g.load_data();
+      bool inflight = next_chunk();  // the chunk staged during this one is real
+      static_for<NL>([&](auto y) { stage_one(0, y); });
+      bool tabs = inflight && next_chunk();  // so is the one after it
+      __syncthreads();
+      static_for<NS>([&](auto s) {
+        static_for<FR>([&](auto f) { fetch_resident(0, s, f); });
+        fetch_streamed(0, s, int_c<0>{});
+      });
+      for (int buf = 0;; buf ^= 1) {
+        const bool flush = (flushes & 1u) != 0;
+        flushes >>= 1;
+        --ahead;
+        // One streamed fragment after another; beside the products, the next one's operands are read
+        // and the staged chunk is stored and loaded again, a little at a time (all reads of a chunk
+        // in one run after the barrier left the matrix pipe idle meanwhile: both waves of a SIMD come
+        // from one workgroup and wait at the same barrier).  The barrier comes before the last
+        // fragment's products: by then every wave holds its operands of this chunk and has stored
+        // its part of the next one, whose first operands are read under those products as soon as
+        // their registers are free.  Aligned ladder at O=64, V=320 on 128 x 128 tiles: 113 -> 109 ms,
+        // 1234 TFLOP/s of bfloat16 products, where this card's library product of 8192 x 8192
+        // matrices reaches 1319: the board's power bounds both.
+        __builtin_amdgcn_s_setprio(1);
+        static_for<FS>([&](auto f) {
+          if constexpr (f() == FS - 1) __syncthreads();
+          static_for<NX>([&](auto x) {
+            constexpr int p = x() / FR, fr = x() % FR, i = SA ? f() : fr, j = SA ? fr : f();
+            f4_t& sum = p == 0 ? lead[i][j] : rest[i][j];
+            sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(SA ? str[f() & 1][PA[p]] : res[PA[p]][fr],
+                                                           SA ? res[PB[p]][fr] : str[f() & 1][PB[p]], sum, 0, 0, 0);
+            if constexpr (f() + 1 < FS) {
+              if constexpr (x() < NS) fetch_streamed(buf, x, int_c<f() + 1>{});
+              constexpr int at = f() * NX + x(), y0 = at * NL / NSTAGE, y1 = (at + 1) * NL / NSTAGE;
+              static_for<y1 - y0>([&](auto y) { stage_one(buf ^ 1, int_c<y0 + y()>{}); });
+            } else {
+              if constexpr (x() < NS) fetch_streamed(buf ^ 1, x, int_c<0>{});
+              static_for<NS>([&](auto s) {
+                if constexpr (p == last_use(s())) fetch_resident(buf ^ 1, s, int_c<fr>{});
+              });
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          });
+        });
+        __builtin_amdgcn_s_setprio(0);
+        const bool tabs_next = tabs && next_chunk();
+        if (flush) flush_window();
+        if (!inflight) break;
+        inflight = tabs;
+        tabs = tabs_next;
+      }
+    }
+  } else if (pb < pe) {
+    auto store = [&](int b) {  // one packed element: its NS slices to NS planes
+      unsigned short* As16 = reinterpret_cast<unsigned short*>(As[b]);
+      unsigned short* Bs16 = reinterpret_cast<unsigned short*>(Bs[b]);
 #pragma unroll
-        for (int e = 0; e < G::BE; ++e) {
-          const int o = g.b_lds_row(e) * LD + g.b_lds_k(e);
+      for (int e = 0; e < G::AE; ++e) {
+        const int o = g.a_lds_row(e) * LD + g.a_lds_k(e);
 #pragma unroll
-          for (int s = 0; s < NS; ++s) Bs16[s * NT * LD + o] = (unsigned short)(g.rb[e] >> (16 * s));
-        }
+        for (int s = 0; s < NS; ++s) As16[s * MT * LD + o] = (unsigned short)(g.ra[e] >> (16 * s));
+      }
+#pragma unroll
+      for (int e = 0; e < G::BE; ++e) {
+        const int o = g.b_lds_row(e) * LD + g.b_lds_k(e);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) Bs16[s * NT * LD + o] = (unsigned short)(g.rb[e] >> (16 * s));
       }
     };
     auto compute = [&](int b, bool flush, auto&& stage, auto&& post) {
@@ -618,18 +721,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_contract_bf16s(ContractParam
       }
       __builtin_amdgcn_s_setprio(0);
       post();  // bookkeeping of the next chunk while the MFMAs drain
-      if (flush) {  // end of a promotion window or of a pair: float32 sums into float64
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              acc[i][j][r] += (double)lead[i][j][r] + (double)rest[i][j][r];
-              lead[i][j][r] = 0.f;
-              rest[i][j][r] = 0.f;
-            }
-      }
+      if (flush) flush_window();
     };
     chunk_pipeline<KT, kSplitWindow>(g, pairs, pb, pe, pool, Ap, Bp, w, blk.mext, blk.next, store, compute);
   }
