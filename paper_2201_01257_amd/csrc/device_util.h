@@ -27,6 +27,8 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_each(f, std::make_integer_sequence<int, N>{});
 }
 
+constexpr int min_c(int a, int b) { return a < b ? a : b; }
+
 // Loads through explicit address spaces: per-lane table reads as global loads (not flat), and
 // wave-uniform descriptor reads as scalar loads from the constant address space (the descriptors
 // are never written while a kernel runs).

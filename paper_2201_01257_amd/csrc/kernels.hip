@@ -161,7 +161,6 @@ __device__ __forceinline__ void lds_store(double* dst, const double* v) {
 
 // The register that holds the die (XCC) a wave runs on: id 20, offset 0, 4 bits.
 constexpr int kXccIdReg = 20 | (0 << 6) | ((4 - 1) << 11);
-constexpr int min_c(int a, int b) { return a < b ? a : b; }
 
 // One work item whose tile takes FM x FN fragments of 16 x 16 per wave: at most (16 WGM FM) x
 // (16 WGN FN) elements, the last ones possibly past the item's rows or columns.  FMX, FNX: the

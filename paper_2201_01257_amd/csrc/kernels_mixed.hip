@@ -316,19 +316,31 @@ __device__ __forceinline__ void epilogue_f32layout(const ProblemDesc& pr, const 
 
 // ---------------------------------------------------------------------------------------------
 // float32 products (v_mfma_f32_16x16x4_f32), float32 window sums promoted to float64.
+//
+// Bound by the products on large blocks: float32 MFMAs take half the time of float64 ones on the
+// same float64 traffic, so what a wave issues beside them weighs double.  LDS holds a row's chunk by
+// lane quarter (slot), so that one 16-byte read gives a lane its operands of all four k-steps; the
+// stores and loads of the staged chunk go between the products of the first k-steps, and the barrier
+// comes before the last one's, under which the next chunk's operands are read.  Ladder at O=32,
+// V=160, tiles of 32: 2.52 -> 2.12 ms (99 TFLOP/s; this card's library product of 8192 x 8192
+// matrices reaches 153) on 128 x 128 with eight waves, 2.64 -> 2.35 on 128 x 64.
 // ---------------------------------------------------------------------------------------------
 template <int MT, int NT, int KT, int WGM, int WGN, bool A_KC, bool B_KC>
-__global__ __launch_bounds__(64 * WGM * WGN) void k_contract_f32(ContractParams P) {
+__global__ __launch_bounds__(64 * WGM * WGN, MT * NT <= 64 * 64 ? 4 : WGM * WGN / 4) void k_contract_f32(ContractParams P) {
   constexpr int NTHR = 64 * WGM * WGN;
   constexpr int WM = MT / WGM, WN = NT / WGN, FM = WM / 16, FN = WN / 16;
-  constexpr int LD = KT + 4;  // floats; rows 16 apart land on distinct banks for the 4 k lanes
+  constexpr int NS = KT / 4;  // MFMA k-steps per chunk
+  constexpr int LD = KT + 4;  // floats: 16 rows' 16-byte operands start on distinct bank quadruples
   static_assert(kSplitWindow % KT == 0, "chunks tile the promotion window");
+  static_assert(NS == 4, "a lane's operands of a chunk in one 16-byte read");
+  // LDS position of k within a row: lane quarter k % 4 reads its operands of all k-steps at once
+  auto slot = [](int k) { return k % 4 * NS + k / 4; };
   using G = Gather<MT, NT, KT, NTHR, A_KC, B_KC, double>;
-  __shared__ float As[2][MT * LD];
-  __shared__ float Bs[2][NT * LD];
+  __shared__ __attribute__((aligned(16))) float As[2][MT * LD];
+  __shared__ __attribute__((aligned(16))) float Bs[2][NT * LD];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WGM, wn = wave / WGM, lr = lane & 15, lq = lane >> 4;
-  const int a_frag = (wm * WM + lr) * LD + lq, b_frag = (wn * WN + lr) * LD + lq;
+  const int a_frag = (wm * WM + lr) * LD + lq * NS, b_frag = (wn * WN + lr) * LD + lq * NS;
   const int item = blockIdx.x;
   if (item >= P.n_work) return;
   const WorkItem w = wave_uniform(sload(P.work + item));
@@ -351,39 +363,68 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_contract_f32(ContractParams 
       part[i][j] = (f4_t){0.f, 0.f, 0.f, 0.f};
     }
   if (pb < pe) {
-    auto store = [&](int b) {
-#pragma unroll
-      for (int e = 0; e < G::AE; ++e) As[b][g.a_lds_row(e) * LD + g.a_lds_k(e)] = (float)g.ra[e];
-#pragma unroll
-      for (int e = 0; e < G::BE; ++e) Bs[b][g.b_lds_row(e) * LD + g.b_lds_k(e)] = (float)g.rb[e];
+    constexpr int NF = FM * FN, NR = FM + FN, AL = G::MA::L, NL = AL + G::MB::L;
+    constexpr int NX = NF * NS, NP = NF * (NS - 1);  // products of a chunk, of all its k-steps but the last
+    // A chunk's operands, k-step s in component s: A fragments, then B fragments.  Two sets, so that
+    // the next chunk's are read under the last products of this one; one on 64 x 64 tiles, where 32
+    // registers less let four workgroups share a compute unit, whose products cover each other's reads.
+    constexpr int SETS = NF <= 4 ? 1 : 2;
+    f4_t op[SETS][NR];
+    auto fetch = [&](int b, auto set, auto r) {
+      if constexpr (r() < FM) op[set() % SETS][r()] = *reinterpret_cast<const f4_t*>(&As[b][a_frag + r() * 16 * LD]);
+      else op[set() % SETS][r()] = *reinterpret_cast<const f4_t*>(&Bs[b][b_frag + (r() - FM) * 16 * LD]);
     };
-    auto compute = [&](int b, bool flush, auto&& stage, auto&& post) {
-      const float* as = As[b] + a_frag;
-      const float* bs = Bs[b] + b_frag;
-      float af[2][FM], bf[2][FN];
-#pragma unroll
-      for (int i = 0; i < FM; ++i) af[0][i] = as[i * 16 * LD];
-#pragma unroll
-      for (int j = 0; j < FN; ++j) bf[0][j] = bs[j * 16 * LD];
+    auto restage = [&](int b, auto y) {  // staged load y (A's, then B's): to LDS, and from memory again
+      constexpr int e = y() < AL ? y() : y() - AL;
+      if constexpr (y() < AL) As[b][g.a_lds_row(e) * LD + slot(g.a_lds_k(e))] = (float)g.ra[e];
+      else Bs[b][g.b_lds_row(e) * LD + slot(g.b_lds_k(e))] = (float)g.rb[e];
+      g.load_one(y());
+    };
+    ChunkWalk<KT, G, double> walk(g, pairs, pb, pe, pool, pr.A, pr.B, w, blk.mext, blk.next);
+    uint32_t flushes = 0;  // of the chunks fetched and not yet multiplied, the oldest in bit 0
+    int ahead = 0;
+    auto note = [&]() {
+      const int kend = walk.k + KT;
+      flushes |= (kend >= walk.d.kext || kend % kSplitWindow == 0 ? 1u : 0u) << ahead;
+      ++ahead;
+    };
+    auto next_chunk = [&]() {
+      const bool more = walk.next_tables();
+      if (more) note();
+      return more;
+    };
+    walk.setup();
+    g.load_tables(walk.d, pool, 0);
+    note();
+    g.load_data();
+    bool inflight = next_chunk();  // the chunk staged during this one is real
+    static_for<NL>([&](auto y) { restage(0, y); });
+    bool tabs = inflight && next_chunk();  // so is the one after it
+    __syncthreads();
+    static_for<NR>([&](auto r) { fetch(0, int_c<0>{}, r); });
+    // one chunk, its operands in set SET; false after the last one
+    auto chunk = [&](auto set) {
+      constexpr int SET = set();
+      const bool flush = (flushes & 1u) != 0;
+      flushes >>= 1;
+      --ahead;
       __builtin_amdgcn_s_setprio(1);  // MFMA phase first when waves of two workgroups compete
-#pragma unroll
-      for (int s = 0; s < KT / 4; ++s) {  // zeros beyond a ragged chunk's K extent
-        const int cur = s & 1, nxt = cur ^ 1;
-        if (s + 1 < KT / 4) {
-#pragma unroll
-          for (int i = 0; i < FM; ++i) af[nxt][i] = as[i * 16 * LD + 4 * (s + 1)];
-#pragma unroll
-          for (int j = 0; j < FN; ++j) bf[nxt][j] = bs[j * 16 * LD + 4 * (s + 1)];
+      static_for<NX>([&](auto x) {  // zeros beyond a ragged chunk's K extent
+        constexpr int st = x() / NF, i = x() % NF / FN, j = x() % FN;
+        if constexpr (x() == NP) __syncthreads();
+        part[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(op[SET % SETS][i][st], op[SET % SETS][FM + j][st], part[i][j], 0, 0, 0);
+        if constexpr (x() < NP) {
+          constexpr int y0 = min_c(x() * NL * 4 / (NP * 3), NL), y1 = min_c((x() + 1) * NL * 4 / (NP * 3), NL);
+          static_for<y1 - y0>([&](auto y) { restage(SET ^ 1, int_c<y0 + y()>{}); });
+        } else if constexpr (SETS == 2) {
+          constexpr int r0 = (x() - NP) * NR / NF, r1 = (x() - NP + 1) * NR / NF;
+          static_for<r1 - r0>([&](auto r) { fetch(SET ^ 1, int_c<SET ^ 1>{}, int_c<r0 + r()>{}); });
         }
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-            part[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[cur][i], bf[cur][j], part[i][j], 0, 0, 0);
-        if (s == 0) stage();
-      }
+        __builtin_amdgcn_sched_barrier(0);
+      });
       __builtin_amdgcn_s_setprio(0);
-      post();  // bookkeeping of the next chunk while the MFMAs drain
+      if constexpr (SETS == 1) static_for<NR>([&](auto r) { fetch(SET ^ 1, set, r); });
+      const bool tabs_next = tabs && next_chunk();
       if (flush) {  // end of a promotion window or of a pair: float32 sums into float64
 #pragma unroll
         for (int i = 0; i < FM; ++i)
@@ -395,8 +436,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_contract_f32(ContractParams 
               part[i][j][r] = 0.f;
             }
       }
+      const bool more = inflight;
+      inflight = tabs;
+      tabs = tabs_next;
+      return more;
     };
-    chunk_pipeline<KT, kSplitWindow>(g, pairs, pb, pe, pool, pr.A, pr.B, w, blk.mext, blk.next, store, compute);
+    while (chunk(int_c<0>{}) && chunk(int_c<1>{})) {}
   }
   epilogue_f32layout<MT, NT, WM, WN, FM, FN>(pr, w, blk, acc, wm, wn, lr, lq);
 }
