@@ -777,21 +777,24 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_contract_bf16s(ContractParam
 // configurations and dispatch
 // ---------------------------------------------------------------------------------------------
 static const MixedConfig kF32Configs[] = {
-    {64, 64, 16, 2, 2, "f32_m64n64k16_w2x2"},
-    {128, 64, 16, 2, 2, "f32_m128n64k16_w2x2"},
-    {64, 128, 16, 2, 2, "f32_m64n128k16_w2x2"},
-    {128, 128, 16, 2, 2, "f32_m128n128k16_w2x2"},
-    {128, 128, 16, 4, 2, "f32_m128n128k16_w4x2"},
-    {128, 128, 16, 2, 4, "f32_m128n128k16_w2x4"},
+    {64, 64, 16, 2, 2, 4, 84, 84, "f32_m64n64k16_w2x2"},
+    {128, 64, 16, 2, 2, 2, 90, 90, "f32_m128n64k16_w2x2"},
+    {64, 128, 16, 2, 2, 2, 90, 90, "f32_m64n128k16_w2x2"},
+    {128, 128, 16, 2, 2, 1, 83, 83, "f32_m128n128k16_w2x2"},
+    {128, 128, 16, 4, 2, 1, 99, 99, "f32_m128n128k16_w4x2"},
+    {128, 128, 16, 2, 4, 1, 99, 99, "f32_m128n128k16_w2x4"},
 };
+// Eight waves where one workgroup fills a compute unit's LDS (two waves per SIMD): four on the same
+// tile were slower on both layouts (aligned ladder at O=24, V=104 1.04 against 0.88 ms; at O=64,
+// V=320 139 against 109, on 128 x 128).  4 x 2 waves read the planes best, 2 x 4 the packed words.
 static const MixedConfig kBf16Configs[] = {
-    {64, 64, 32, 2, 2, "bf16s_m64n64k32_w2x2"},
-    {128, 64, 32, 2, 2, "bf16s_m128n64k32_w2x2"},
-    {64, 128, 32, 2, 2, "bf16s_m64n128k32_w2x2"},
-    {128, 64, 32, 4, 2, "bf16s_m128n64k32_w4x2"},
-    {64, 128, 32, 2, 4, "bf16s_m64n128k32_w2x4"},
-    {128, 128, 32, 4, 2, "bf16s_m128n128k32_w4x2"},
-    {128, 128, 32, 2, 4, "bf16s_m128n128k32_w2x4"},
+    {64, 64, 32, 2, 2, 2, 61, 100, "bf16s_m64n64k32_w2x2"},
+    {128, 64, 32, 2, 2, 1, 55, 97, "bf16s_m128n64k32_w2x2"},
+    {64, 128, 32, 2, 2, 1, 50, 97, "bf16s_m64n128k32_w2x2"},
+    {128, 64, 32, 4, 2, 1, 73, 110, "bf16s_m128n64k32_w4x2"},
+    {64, 128, 32, 2, 4, 1, 64, 110, "bf16s_m64n128k32_w2x4"},
+    {128, 128, 32, 4, 2, 1, 50, 125, "bf16s_m128n128k32_w4x2"},
+    {128, 128, 32, 2, 4, 1, 92, 120, "bf16s_m128n128k32_w2x4"},
 };
 
 int mixed_config_count(int precision) {

@@ -45,6 +45,9 @@ struct PrepParams {
 
 struct MixedConfig {
   int mt, nt, kt, wgm, wgn;
+  int resident;          // workgroups that fit on a compute unit
+  double tflops;         // measured on large blocks: float32; split bfloat16 (aligned) on the packed layout
+  double tflops_planes;  // and on the planes layout
   const char* name;
 };
 

@@ -567,19 +567,22 @@ struct TileCfg {
   int mt, nt, kt, threads;
   int um, un;  // rows and columns of one step of the tile size (16 per wave along the dimension)
   int resident;  // workgroups that fit on a compute unit
-  double rate;   // flop/s of the whole chip on large blocks
+  double rate;   // flop/s of the whole chip on large blocks (of the products asked for, not of their slices)
   const char* name;
 };
 
 static int cfg_count(int prec) { return prec == TAMM_PREC_F64 ? f64_config_count() : mixed_config_count(prec); }
 
-static TileCfg cfg_get(int prec, int c) {
+// planes: rates of the split-bfloat16 kernels on the planes layout, else on the packed one
+static TileCfg cfg_get(int prec, int c, bool planes = false) {
   if (prec == TAMM_PREC_F64) {
     const F64Config& f = f64_config(c);
     return TileCfg{f.mt, f.nt, f.kt, 64 * f.wgm * f.wgn, 16 * f.wgm, 16 * f.wgn, f.resident, f.tflops * 1e12, f.name};
   }
   const MixedConfig& f = mixed_config(prec, c);
-  return TileCfg{f.mt, f.nt, f.kt, 64 * f.wgm * f.wgn, f.mt, f.nt, 1, 1e14, f.name};
+  // three slices multiply 6 pairs instead of 10, on the same gathers
+  const double rate = (planes ? f.tflops_planes : f.tflops) * (prec == TAMM_PREC_BF16X3 ? 1.35e12 : 1e12);
+  return TileCfg{f.mt, f.nt, f.kt, 64 * f.wgm * f.wgn, f.mt, f.nt, f.resident, rate, f.name};
 }
 
 // Number of output tiles and padding factor of one configuration.
@@ -596,25 +599,6 @@ static std::pair<int64_t, double> tiles_for(const tamm_plan* p, int c) {
   return std::make_pair(n, useful > 0 ? area / useful : 1.0);
 }
 
-// Default configuration of the reduced-precision kernels when the autotuner has not run: the largest
-// tile that gives every compute unit two tiles with little padding.
-static int default_config(const tamm_plan* p) {
-  int best = 0;
-  double best_score = -1;
-  for (int c = 0; c < cfg_count(p->prec); ++c) {
-    auto tw = tiles_for(p, c);
-    const TileCfg f = cfg_get(p->prec, c);
-    if (f.threads != 256 || f.mt > 128 || f.nt > 128) continue;
-    double score = (double)f.mt * f.nt / tw.second;
-    if (tw.first < 512) score *= (double)tw.first / 512.0;
-    if (score > best_score) {
-      best_score = score;
-      best = c;
-    }
-  }
-  return best;
-}
-
 // K splits of a block's tiles: in proportion to its summed K extent, the heaviest blocks' get
 // k_splits parts, lighter ones fewer (at least one), so that the parts cost about the same.
 static int block_splits(int k_splits, double kext, double max_kext) {
@@ -622,7 +606,7 @@ static int block_splits(int k_splits, double kext, double max_kext) {
   return (int)std::min<double>(k_splits, std::max(1.0, std::floor(k_splits * kext / max_kext + 0.5)));
 }
 
-// Estimated time in microseconds of a float64 contraction over blocks of these shapes: the larger of
+// Estimated time in microseconds of a contraction over blocks of these shapes: the larger of
 // the longest item and the items' sum over the resident workgroups plus part of an item for the
 // tail, at least the time of the unavoidable traffic.  An item takes, per chunk of summed
 // indices, its products at the configuration's rate or one memory round trip, whichever is longer;
@@ -630,9 +614,12 @@ static int block_splits(int k_splits, double kext, double max_kext) {
 // were fitted to 108 contractions (3 kF to 6 TF, tiles of 3 to 64) timed with every configuration and
 // 1 to 16 K splits: taking the configuration with the least estimate costs 4 % against the best one
 // of each on average (up to 20 %), the rule before it (largest tile, no padding, two tiles per
-// compute unit) 14 % (up to 63 %).
+// compute unit) 14 % (up to 63 %).  The reduced precisions share them but for the tail, which the
+// dispatcher's rotation makes longer than the queues do; over 26 contractions in each of them the
+// least estimate costs 2-4 %, the rule before it 15 % in float32 and 20-40 % in split bfloat16, which
+// it ran on four-wave tiles.
 constexpr double kRoundTrip16 = 0.60, kRoundTrip32 = 0.70, kRoundTripWave = 0.78;  // a chunk of 16, of 32, of a one-wave workgroup
-constexpr double kPair = 0.137, kItem = 3.84, kPer1024 = 0.63, kTail = 0.42, kGroupTail = 0.3;
+constexpr double kPair = 0.137, kItem = 3.84, kPer1024 = 0.63, kTail = 0.42, kTailMixed = 0.7, kGroupTail = 0.3;
 constexpr double kReduce = 5.6, kReduceBytes = 5.0e6;  // launch, bytes per microsecond
 
 static double item_us(const BlockShape& b, const TileCfg& f, double area, double parts) {
@@ -654,7 +641,7 @@ static void for_tiles(const BlockShape& b, const TileCfg& f, int64_t tm, int64_t
     }
 }
 
-static double estimate_us(const std::vector<BlockShape>& shapes, const TileCfg& f, int k_splits, double bytes) {
+static double estimate_us(const std::vector<BlockShape>& shapes, const TileCfg& f, int k_splits, double bytes, double tail) {
   const double slots = (double)f.resident * kComputeUnits;
   double max_kext = 0, total = 0, longest = 0, items = 0, partial = 0;
   for (const BlockShape& b : shapes) max_kext = std::max(max_kext, b.kext);
@@ -669,7 +656,7 @@ static double estimate_us(const std::vector<BlockShape>& shapes, const TileCfg& 
     });
     if (ns > 1) partial += (double)(b.mext * b.next * b.count) * ns;
   }
-  double t = items > slots ? std::max(longest, total / slots + kTail * longest) : longest;
+  double t = items > slots ? std::max(longest, total / slots + tail * longest) : longest;
   t = std::max(t, bytes / (f.resident > 2 ? 4.8e6 : 3.8e6));  // what copies reach with many and with few workgroups in flight
   return t + (partial > 0 ? kReduce + partial * 16.0 / kReduceBytes : 0.0);
 }
@@ -716,10 +703,11 @@ static double group_estimate_us(const std::vector<BlockShape>& shapes, const Til
   return std::max(std::max(longest, total / slots + kGroupTail * longest), bytes / (f.resident > 2 ? 4.8e6 : 3.8e6));
 }
 
-// Default configuration and K splits of a float64 plan: the least estimate; more splits only where
-// they are estimated to gain 3 %, and 8 % above a millisecond, where the queues have filled the tail
+// Default configuration and K splits of a plan: the least estimate; more splits only where they are
+// estimated to gain 3 %, and in float64 8 % above a millisecond, where the queues have filled the tail
 // that splits would (ladder and its gradients at O=32, V=160: 3.1 ms in one part, 3.4 in four).  The partial tiles take at most an eighth of the tensors' bytes or 64 MiB.
-static std::pair<int, int> default_f64(const tamm_plan* p, int config, int k_splits) {
+static std::pair<int, int> default_work(const tamm_plan* p, int config, int k_splits) {
+  const bool f64 = p->prec == TAMM_PREC_F64;
   const double bytes = p->stats.algorithmic_bytes, budget = std::max(bytes / 8, (double)(64 << 20));
   double best = 1e300, max_kext = 0;
   std::pair<int, int> pick(std::max(config, 0), std::max(k_splits, 1));
@@ -729,22 +717,22 @@ static std::pair<int, int> default_f64(const tamm_plan* p, int config, int k_spl
     const int splits = k_splits > 0 ? k_splits : ks;
     double least = 1e300;
     int at = -1;
-    for (int c = 0; c < f64_config_count(); ++c) {
-      if (config >= 0 ? c != config : f64_config_canonical(c) != c) continue;
-      const TileCfg f = cfg_get(p->prec, c);
+    for (int c = 0; c < cfg_count(p->prec); ++c) {
+      if (config >= 0 ? c != config : f64 && f64_config_canonical(c) != c) continue;
+      const TileCfg f = cfg_get(p->prec, c, p->planes);
       double need = 0;
       for (const BlockShape& b : p->shapes) {
         const int ns = block_splits(splits, b.kext, max_kext);
         if (ns > 1) need += 8.0 * f.mt * f.nt * ns * (double)(((b.mext + f.mt - 1) / f.mt) * ((b.next + f.nt - 1) / f.nt) * b.count);
       }
       if (k_splits <= 0 && need > budget) continue;
-      const double t = estimate_us(p->shapes, f, splits, bytes);
+      const double t = estimate_us(p->shapes, f, splits, bytes, f64 ? kTail : kTailMixed);
       if (t < least) {
         least = t;
         at = c;
       }
     }
-    if (at >= 0 && least < (best > 1000.0 ? 0.92 : 0.97) * best) {
+    if (at >= 0 && least < (f64 && best > 1000.0 ? 0.92 : 0.97) * best) {
       best = least;
       pick = std::make_pair(at, splits);
     }
@@ -898,21 +886,9 @@ static int configure_work(tamm_plan* p, int config, int k_splits) {
   const int ncfg = cfg_count(p->prec);
   const int64_t nob = (int64_t)p->blocks.size();
   if (config >= ncfg) return fail(TAMM_ERR_ARG, "kernel configuration %d does not exist (%d available)", config, ncfg);
-  if (p->prec == TAMM_PREC_F64 && (config < 0 || k_splits <= 0)) std::tie(config, k_splits) = default_f64(p, config, k_splits);
-  if (config < 0) config = default_config(p);
+  if (config < 0 || k_splits <= 0) std::tie(config, k_splits) = default_work(p, config, k_splits);
   const TileCfg f = cfg_get(p->prec, config);
   const int64_t ntiles = tiles_for(p, config).first;
-  if (k_splits <= 0) {
-    k_splits = 1;
-    // output-starved operations: split K so that there are about two tiles per compute unit
-    if (ntiles > 0 && ntiles < 512) {
-      double maxk = 0;
-      for (double c : p->block_cost) maxk = std::max(maxk, c);
-      const int want = (int)((512 + ntiles - 1) / ntiles);
-      const int kmax = (int)std::max(1.0, maxk / (4.0 * f.kt));
-      k_splits = std::max(1, std::min({want, 16, kmax}));
-    }
-  }
   if (k_splits > 64) return fail(TAMM_ERR_ARG, "k_splits must be in [1, 64]");
   struct Tile {
     double cost;
