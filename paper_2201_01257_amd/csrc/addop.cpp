@@ -90,7 +90,7 @@ extern "C" int tamm_add_create(tamm_tensor* out, const char* out_lbl, const tamm
       const int64_t nbatch = n / ((int64_t)ey * ex);
       for (int64_t t = 0; t < nbatch; ++t)
         for (int y = 0; y < ey; y += 32)
-          for (int x = 0; x < ex; x += 32) a->items.push_back(AddItem{b, (int32_t)t, y, x});
+          for (int x = 0; x < ex; x += 32 * kAddTiles) a->items.push_back(AddItem{b, (int32_t)t, y, x});
     }
     if (a->items.size() > (size_t)INT32_MAX) return fail(TAMM_ERR_UNSUPPORTED, "too many work items");
   }

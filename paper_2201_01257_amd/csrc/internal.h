@@ -195,6 +195,7 @@ struct AddBlock {
 struct AddItem {
   int32_t block, a, b, c;
 };
+constexpr int kAddTiles = 2;  // 32 x 32 tiles side by side (along out's last dimension) of a transpose-mode item
 
 struct AddParams {
   double* out;

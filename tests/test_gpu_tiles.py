@@ -1,8 +1,8 @@
 """Float64 tiles of every size a configuration can have (whole tiles, the even cuts of a block's end,
 the smallest blocks), in both operand orientations, with and without K splits, and the queues of a
-persistent launch, against float64 products computed by NumPy.
+persistent launch, against float64 products computed by NumPy; and the reduced precisions' chunks.
 
-The tolerance is that of a sum of K products in another order: 2 K u (u = 2^-53) of the sum of
+The tolerance (float64) is that of a sum of K products in another order: 2 K u (u = 2^-53) of the sum of
 magnitudes, element by element."""
 
 import numpy as np
@@ -82,3 +82,28 @@ def test_group_of_a_long_sum_and_a_wide_product():
         torch.cuda.synchronize()
         for (C, A, B), alpha in zip(refs, (1.5, 1.0, -1.0)):
             check(C, A, B, alpha, 0.0, np.zeros((A.shape[0], B.shape[1])))
+
+
+@pytest.mark.parametrize("precision", ["f32", "bf16x3", "bf16x4_aligned"])
+@pytest.mark.parametrize("a_kc,b_kc", [(True, True), (True, False), (False, True), (False, False)])
+@pytest.mark.parametrize("ext", [(1, 17), (64, 65), (129, 63), (200, 130)])
+def test_reduced_precision_chunks_and_windows(ext, a_kc, b_kc, precision):
+    # summed tiles of every remainder of a chunk and of one 256-long window and a little more or
+    # less; small integers, which every precision holds and sums exactly (sums below 2^24)
+    m, n = ext
+    k_tiles = [[16, 8, 256, 520], [7, 1, 255, 257, 33]][m % 2]
+    k = sum(k_tiles)
+    rng = np.random.default_rng(m)
+    A, B = rng.integers(-8, 9, (m + 3, k)).astype(float), rng.integers(-8, 9, (k, n + 5)).astype(float)
+    sm, sk, sn = (tm.Space.explicit(t) for t in ([m, 3], k_tiles, [5, n]))
+    ta = tm.Tensor([sm, sk] if a_kc else [sk, sm]).from_dense(A if a_kc else A.T)
+    tb = tm.Tensor([sn, sk] if b_kc else [sk, sn]).from_dense(B.T if b_kc else B)
+    C = tm.Tensor([sm, sn], device="cuda")
+    plan = tm.Plan(C, "ij", ta, "ik" if a_kc else "ki", tb, "jk" if b_kc else "kj", precision=precision)
+    for config in range(plan.config_count()):
+        for ks in (1, 2):
+            plan.set_config(config, ks)
+            C.data.fill_(float("nan"))
+            plan.execute(1.0, 0.0)
+            torch.cuda.synchronize()
+            assert np.array_equal(C.to_dense(), A @ B), (plan.config_name(), ks)
