@@ -21,6 +21,7 @@
 //           its own accumulator, and only the small residual products see float32 rounding.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "device_util.h"
@@ -91,176 +92,202 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
+// Block of a wave's item (the same for the whole wave), through scalar loads: the search is a chain
+// of dependent ones.
 __device__ __forceinline__ int find_block(const PrepBlock* blocks, int n, int64_t item) {
   int lo = 0, hi = n - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (blocks[mid].item0 <= item) lo = mid;
+    if (sload(&blocks[mid].item0) <= item) lo = mid;
     else hi = mid - 1;
   }
   return lo;
 }
 
-// Planes layout, lanes along k: a wave converts kPrepUnroll consecutive (block, row, window)
-// items, 4 consecutive k of one row per lane and item.  The loads of all its items are issued
-// before any of them is converted, so each wave keeps kPrepUnroll windows of reads in flight.
-constexpr int kPrepUnroll = 4;
+// Lanes along k (the operand's stride-1 label is summed): a wave converts kPrepUnroll consecutive
+// (block, row, window) items, the maximum of a window is a wave reduction.  Planes layout: 4
+// consecutive k of one row per lane and item; packed: k = lane + 64 j.  The loads of all its items
+// are issued before any of them is converted, so each wave keeps that many windows of reads in flight
+// (one in the packed layout, whose K extents are mostly far below a window: four rows of a dozen
+// elements after one another only made the chain of descriptor loads longer, 23 -> 30 us for the
+// T1 occupied term at O=13, V=102).
+template <bool PLANES>
+constexpr int kPrepUnroll = PLANES ? 4 : 1;
 
-__device__ __forceinline__ void prep_planes_kc(const PrepParams& P, int64_t first, int lane) {
+template <bool PLANES>
+__device__ __forceinline__ void prep_k_along_lanes(const PrepParams& P, int64_t first, int lane) {
   static_assert(kSplitWindow == 4 * 64, "a wave converts one window, 4 k per lane");
   typedef double d2_t __attribute__((ext_vector_type(2)));
+  constexpr int U = kPrepUnroll<PLANES>;
+  if (first >= P.n_items) return;
   const int32_t* __restrict__ pool = P.pool;
-  double x[kPrepUnroll][4];
-  int64_t pos[kPrepUnroll];
-  bool live[kPrepUnroll];
+  double x[U][4];
+  int64_t pos[U];   // planes: element of the first k; packed: the row
+  int32_t t[U][4];  // table entries
+  int nk[U];        // k of this lane in the window (planes: 0 or 4)
+  int b = find_block(P.blocks, P.n_blocks, first);
 #pragma unroll
-  for (int u = 0; u < kPrepUnroll; ++u) {
+  for (int u = 0; u < U; ++u) {
     const int64_t item = first + u;
-    live[u] = false;
+    nk[u] = 0;
     pos[u] = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) x[u][i] = 0.0;
     if (item >= P.n_items) continue;  // wave-uniform
-    const PrepBlock pb = P.blocks[find_block(P.blocks, P.n_blocks, item)];
+    while (b + 1 < P.n_blocks && sload(&P.blocks[b + 1].item0) <= item) ++b;
+    const PrepBlock pb = sload(P.blocks + b);
     const int64_t local = item - pb.item0;
     const int k0 = (int)(local % pb.nwin) * kSplitWindow, row = (int)(local / pb.nwin);
-    const int k = k0 + 4 * lane;
     const int k1 = min(pb.kext, k0 + kSplitWindow);
-    pos[u] = pb.off + (int64_t)row * pb.kext + k;
-    live[u] = k < k1;  // k1 is a multiple of 8: all four k are inside or all outside
-    if (!live[u]) continue;
-    const int64_t rowoff = pb.off + pool[pb.tab_row + row];
-    int32_t t[4];
+    const int64_t rowoff = pb.off + sload(pool + pb.tab_row + row);
+    if constexpr (PLANES) {
+      const int k = k0 + 4 * lane;
+      pos[u] = pb.off + (int64_t)row * pb.kext + k;
+      if (k >= k1) continue;  // k1 is a multiple of 8: all four k are inside or all outside
+      nk[u] = 4;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) t[i] = pool[pb.tab_k + k + i];
-    const int64_t a = rowoff + t[0];
-    if (t[1] == t[0] + 1 && t[2] == t[0] + 2 && t[3] == t[0] + 3 && (a & 1) == 0) {
-      // four consecutive elements at a 16-byte boundary: two 16-byte loads
-      const d2_t lo = *reinterpret_cast<const d2_t*>(P.x + a), hi = *reinterpret_cast<const d2_t*>(P.x + a + 2);
-      x[u][0] = lo[0];
-      x[u][1] = lo[1];
-      x[u][2] = hi[0];
-      x[u][3] = hi[1];
+      for (int i = 0; i < 4; ++i) t[u][i] = pool[pb.tab_k + k + i];
+      const int64_t a = rowoff + t[u][0];
+      if (t[u][1] == t[u][0] + 1 && t[u][2] == t[u][0] + 2 && t[u][3] == t[u][0] + 3 && (a & 1) == 0) {
+        // four consecutive elements at a 16-byte boundary: two 16-byte loads
+        const d2_t lo = *reinterpret_cast<const d2_t*>(P.x + a), hi = *reinterpret_cast<const d2_t*>(P.x + a + 2);
+        x[u][0] = lo[0];
+        x[u][1] = lo[1];
+        x[u][2] = hi[0];
+        x[u][3] = hi[1];
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[u][i] = P.x[rowoff + t[u][i]];
+      }
     } else {
+      pos[u] = rowoff;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) x[u][i] = P.x[rowoff + t[i]];
+      for (int i = 0; i < 4; ++i)
+        if (k0 + lane + 64 * i < k1) {
+          nk[u] = i + 1;
+          t[u][i] = pool[pb.tab_k + k0 + lane + 64 * i];
+          x[u][i] = P.x[rowoff + t[u][i]];
+        }
     }
   }
   const int ns = P.aligned ? 4 : 3;
-  unsigned short* __restrict__ out = static_cast<unsigned short*>(P.out);
 #pragma unroll
-  for (int u = 0; u < kPrepUnroll; ++u) {
+  for (int u = 0; u < U; ++u) {
     if (first + u >= P.n_items) break;  // wave-uniform
     double mx = 0.0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) mx = fmax(mx, fabs(x[u][i]));
     const int e = window_exponent(wave_max(mx));
-    if (!live[u]) continue;
+    if (nk[u] == 0) continue;
     uint64_t w[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) w[i] = P.aligned ? split_aligned(x[u][i], e) : split_plain(x[u][i]);
-    for (int sl = 0; sl < ns; ++sl) {
-      uint64_t v = 0;
+    if constexpr (PLANES) {
+      for (int sl = 0; sl < ns; ++sl) {
+        uint64_t v = 0;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v |= ((w[i] >> (16 * sl)) & 0xFFFFull) << (16 * i);
-      *reinterpret_cast<uint64_t*>(out + sl * P.plane_stride + pos[u]) = v;
+        for (int i = 0; i < 4; ++i) v |= ((w[i] >> (16 * sl)) & 0xFFFFull) << (16 * i);
+        *reinterpret_cast<uint64_t*>(static_cast<unsigned short*>(P.out) + sl * P.plane_stride + pos[u]) = v;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (i < nk[u]) static_cast<uint64_t*>(P.out)[pos[u] + t[u][i]] = w[i];
     }
   }
 }
 
-// One wave per item.  ROWS_ALONG_LANES = false: the operand's stride-1 label is summed, so an item
-// is one (block, row, window) and the lanes run along k (coalesced); the window maximum is a wave
-// reduction.  ROWS_ALONG_LANES = true: an item is (block, 64 rows, window), each lane owns a row
-// and walks the window (lanes coalesce along the row label).
-template <bool ROWS_ALONG_LANES>
-__global__ __launch_bounds__(256) void k_prep_split(PrepParams P) {
-  const int lane = threadIdx.x & 63;
-  if (!ROWS_ALONG_LANES && P.planes) {
-    prep_planes_kc(P, ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kPrepUnroll, lane);
-    return;
-  }
-  const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+// Lanes along the rows (the operand's stride-1 label is not summed): a workgroup converts one (block,
+// 64 rows, window) item, its four waves a quarter of the window each.  A lane holds its row's 64
+// elements in registers: all of them are in flight at once and read once.  (One wave walking the
+// window, twice for the maximum, took 2.0 ms for the 157 million doubles of the amplitudes at O=64,
+// V=320, where this takes 1.3, and most of the time of a small contraction: three-slice ladder at
+// O=12, V=67 in tiles of 11, 192 -> 122 us in all.)
+template <bool PLANES>
+__device__ __forceinline__ void prep_rows_along_lanes(const PrepParams& P, double (&maxima)[4][64]) {
+  constexpr int KW = kSplitWindow / 4;  // k per wave
+  const int lane = threadIdx.x & 63, wave = wave_uniform((int)threadIdx.x >> 6);
+  const int64_t item = blockIdx.x + (int64_t)blockIdx.y * gridDim.x;
   if (item >= P.n_items) return;
-  const int b = find_block(P.blocks, P.n_blocks, item);
-  const PrepBlock pb = P.blocks[b];
+  const PrepBlock pb = sload(P.blocks + find_block(P.blocks, P.n_blocks, item));
   const int64_t local = item - pb.item0;
-  const int win = (int)(local % pb.nwin);
-  const int rg = (int)(local / pb.nwin);
-  const int k0 = win * kSplitWindow;
-  const int k1 = min(pb.kext, k0 + kSplitWindow);
+  const int k0 = (int)(local % pb.nwin) * kSplitWindow + wave * KW;  // this wave's first k
+  const int n = min(KW, min(pb.kext, k0 - wave * KW + kSplitWindow) - k0);  // and how many
+  const int row = (int)(local / pb.nwin) * 64 + lane;
   const int32_t* __restrict__ pool = P.pool;
-  if (P.planes) {
-    // planes layout (every K extent a multiple of 8): a lane converts 4 (lanes along k) or 8
-    // (lanes along rows) consecutive k of one row and writes each slice plane's part at once
-    const int ns = P.aligned ? 4 : 3;
-    unsigned short* __restrict__ out = static_cast<unsigned short*>(P.out);
-    {  // lanes along rows (lanes along k: prep_planes_kc)
-      const int row = rg * 64 + lane;
-      if (row >= pb.rows) return;
-      const int64_t rowoff = pb.off + pool[pb.tab_row + row];
-      double mx = 0.0;
-      if (P.aligned)
-        for (int k = k0; k < k1; ++k) mx = fmax(mx, fabs(P.x[rowoff + pool[pb.tab_k + k]]));
-      const int e = window_exponent(mx);
-      for (int k = k0; k < k1; k += 8) {
-        uint64_t w[8];
+  const int64_t rowoff = pb.off + pool[pb.tab_row + min(row, pb.rows - 1)];
+  const int32_t* __restrict__ tab = pool + pb.tab_k + k0;
+  double x[KW];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const double v = P.x[rowoff + pool[pb.tab_k + k + i]];
-          w[i] = P.aligned ? split_aligned(v, e) : split_plain(v);
-        }
-        const int64_t pos = pb.off + (int64_t)row * pb.kext + k;
-        for (int sl = 0; sl < ns; ++sl) {
-          u4_t v;
+  for (int i = 0; i < KW; ++i) x[i] = 0.0;
+  if (n == KW) {
 #pragma unroll
-          for (int h = 0; h < 4; ++h)
-            v[h] = (uint32_t)((w[2 * h] >> (16 * sl)) & 0xFFFFu) | ((uint32_t)((w[2 * h + 1] >> (16 * sl)) & 0xFFFFu) << 16);
-          *reinterpret_cast<u4_t*>(out + sl * P.plane_stride + pos) = v;
-        }
-      }
-    }
-    return;
-  }
-  if (!ROWS_ALONG_LANES) {
-    const int row = rg;
-    const int64_t rowoff = pb.off + pool[pb.tab_row + row];
-    double x[kSplitWindow / 64];
-    double mx = 0.0;
-#pragma unroll
-    for (int j = 0; j < kSplitWindow / 64; ++j) {
-      const int k = k0 + lane + 64 * j;
-      x[j] = (k < k1) ? P.x[rowoff + pool[pb.tab_k + k]] : 0.0;
-      mx = fmax(mx, fabs(x[j]));
-    }
-    const int e = window_exponent(wave_max(mx));
-#pragma unroll
-    for (int j = 0; j < kSplitWindow / 64; ++j) {
-      const int k = k0 + lane + 64 * j;
-      if (k < k1)
-        static_cast<uint64_t*>(P.out)[rowoff + pool[pb.tab_k + k]] = P.aligned ? split_aligned(x[j], e) : split_plain(x[j]);
-    }
+    for (int i = 0; i < KW; ++i) x[i] = P.x[rowoff + sload(tab + i)];
   } else {
-    const int row = rg * 64 + lane;
-    if (row >= pb.rows) return;
-    const int64_t rowoff = pb.off + pool[pb.tab_row + row];
-    double mx = 0.0;
-    if (P.aligned)
-      for (int k = k0; k < k1; ++k) mx = fmax(mx, fabs(P.x[rowoff + pool[pb.tab_k + k]]));
-    const int e = window_exponent(mx);
-    for (int k = k0; k < k1; ++k) {
-      const int64_t a = rowoff + pool[pb.tab_k + k];
-      const double v = P.x[a];
-      static_cast<uint64_t*>(P.out)[a] = P.aligned ? split_aligned(v, e) : split_plain(v);
+#pragma unroll
+    for (int g = 0; g < KW / 8; ++g) {
+      if (8 * g >= n) continue;  // wave-uniform
+#pragma unroll
+      for (int i = 8 * g; i < 8 * g + 8; ++i) x[i] = P.x[rowoff + sload(tab + min(i, n - 1))];  // past the end: the last again
     }
+  }
+  int e = 0;
+  if (P.aligned) {
+    double mx = 0.0;
+#pragma unroll
+    for (int i = 0; i < KW; ++i) mx = fmax(mx, fabs(x[i]));
+    maxima[wave][lane] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) mx = fmax(mx, maxima[q][lane]);
+    e = window_exponent(mx);
+  }
+  if (row >= pb.rows) return;
+  const int ns = P.aligned ? 4 : 3;
+#pragma unroll
+  for (int g = 0; g < KW / 8; ++g) {
+    if (8 * g >= n) continue;  // wave-uniform
+    uint64_t w[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w[i] = P.aligned ? split_aligned(x[8 * g + i], e) : split_plain(x[8 * g + i]);
+    if constexpr (PLANES) {  // every K extent is a multiple of 8
+      const int64_t pos = pb.off + (int64_t)row * pb.kext + k0 + 8 * g;
+      for (int sl = 0; sl < ns; ++sl) {
+        u4_t v;
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+          v[h] = (uint32_t)((w[2 * h] >> (16 * sl)) & 0xFFFFu) | ((uint32_t)((w[2 * h + 1] >> (16 * sl)) & 0xFFFFu) << 16);
+        *reinterpret_cast<u4_t*>(static_cast<unsigned short*>(P.out) + sl * P.plane_stride + pos) = v;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (8 * g + i < n) static_cast<uint64_t*>(P.out)[rowoff + sload(tab + 8 * g + i)] = w[i];
+    }
+  }
+}
+
+template <bool ROWS_ALONG_LANES, bool PLANES>
+__global__ __launch_bounds__(256) void k_prep_split(PrepParams P) {
+  if constexpr (ROWS_ALONG_LANES) {
+    __shared__ double maxima[4][64];
+    prep_rows_along_lanes<PLANES>(P, maxima);
+  } else {
+    const int wave = wave_uniform((int)threadIdx.x >> 6);
+    prep_k_along_lanes<PLANES>(P, ((int64_t)blockIdx.x * 4 + wave) * kPrepUnroll<PLANES>, threadIdx.x & 63);
   }
 }
 
 hipError_t launch_prep_split(const PrepParams& p, bool rows_along_lanes, hipStream_t s) {
   if (p.n_items <= 0) return hipSuccess;
-  const int64_t per_block = (!rows_along_lanes && p.planes) ? 4 * kPrepUnroll : 4;  // items per workgroup
-  const dim3 g((unsigned)((p.n_items + per_block - 1) / per_block)), b(256);
-  if (rows_along_lanes) hipLaunchKernelGGL(k_prep_split<true>, g, b, 0, s, p);
-  else hipLaunchKernelGGL(k_prep_split<false>, g, b, 0, s, p);
+  const int64_t per_block = rows_along_lanes ? 1 : 4 * (p.planes ? kPrepUnroll<true> : kPrepUnroll<false>);  // items per workgroup
+  // a grid dimension holds fewer than 2^32 threads: long item lists take two
+  const int64_t blocks = (p.n_items + per_block - 1) / per_block, wide = rows_along_lanes ? std::min<int64_t>(blocks, 1 << 20) : blocks;
+  const dim3 g((unsigned)wide, (unsigned)((blocks + wide - 1) / wide)), b(256);
+  if (rows_along_lanes && p.planes) hipLaunchKernelGGL((k_prep_split<true, true>), g, b, 0, s, p);
+  else if (rows_along_lanes) hipLaunchKernelGGL((k_prep_split<true, false>), g, b, 0, s, p);
+  else if (p.planes) hipLaunchKernelGGL((k_prep_split<false, true>), g, b, 0, s, p);
+  else hipLaunchKernelGGL((k_prep_split<false, false>), g, b, 0, s, p);
   return hipGetLastError();
 }
 
