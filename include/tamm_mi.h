@@ -209,7 +209,8 @@ int tamm_plan_stats_get(const tamm_plan* p, tamm_plan_stats* s);
  * are 0..count-1.  tamm_plan_set_config selects one (the autotuner uses this); k_splits >= 1
  * splits the pair range of the output tiles of the heaviest blocks (largest summed K extent)
  * into that many deterministic partial sums, and lighter blocks' tiles into proportionally
- * fewer (at least one); 0 lets the library choose.  Changing the configuration requires
+ * fewer (at least one); 0 lets the library choose.  A plan that was never configured runs the
+ * configuration and K splits with the least estimated time.  Changing the configuration requires
  * re-querying the workspace size and re-binding. */
 int tamm_plan_config_count(const tamm_plan* p, int32_t* count);
 int tamm_plan_set_config(tamm_plan* p, int32_t config, int32_t k_splits);
@@ -217,7 +218,9 @@ int tamm_plan_set_config(tamm_plan* p, int32_t config, int32_t k_splits);
  * longest first; among tiles of equal cost, tile_order 0 keeps the tiles of one output block
  * together, row by row (neighbours share A row panels), and tile_order 1 groups the tiles that
  * read the same B column panel across blocks and rows.  Then the list is cut into chunks of
- * `chunk` items for the chip's eight dies (each with its own L2), chunk c running on die c mod 8;
+ * `chunk` items for the chip's eight dies (each with its own L2), chunk c running on die c mod 8
+ * (in a float64 launch of long items, by default: its workgroups are resident and take items from
+ * their own die's queue, then from the others');
  * 0 keeps the list as it is; -1 restores the library default (32, or the TAMM_XCD_CHUNK
  * environment variable).  The autotuner searches both after the kernel configuration.  Requires
  * re-binding. */
@@ -230,7 +233,8 @@ int tamm_plan_set_order(tamm_plan* p, int32_t tile_order, int32_t chunk);
  * split at the next execution, after the caller changed the values.  No effect on other
  * precisions.  Host only. */
 int tamm_plan_set_constant(tamm_plan* p, int32_t which, int32_t constant);
-/* Human-readable name of a configuration (static string), e.g. "f64_m128n64k16_w2x2_o1". */
+/* Human-readable name of a configuration (static string), e.g. "f64_m128n64k16_w2x2_o1".
+ * Several float64 ids may name the same kernel (ids are stable: cached choices keep their meaning). */
 const char* tamm_config_name(int32_t precision, int32_t config);
 
 /* Autotuner.  Measures every kernel configuration with K splits 1, 2, 4 and 8 that fits the
@@ -332,7 +336,8 @@ int tamm_contract_noalloc(tamm_tensor* out, const char* out_lbl, const tamm_tens
  * Groups: many independent plans executed together (the single-GPU analogue of running the
  * operations of one scheduler level at once, Sec. III-B): one screening launch over every
  * member, then one persistent contraction launch whose workgroups take output tiles of all
- * members, heaviest first, from a shared counter.  Members must be float64 plans; no member may
+ * members, heaviest first, from one queue per die (launches of short items: one workgroup per
+ * tile).  Members must be float64 plans; no member may
  * write storage that another member reads or writes (checked at execution, ERR_ARG).  Plans and
  * their tensors must outlive the group; the group uses its own workspace (the members' own
  * workspaces are not needed).  The group ignores the members' kernel configurations and runs
@@ -345,7 +350,8 @@ int tamm_group_workspace_size(const tamm_group* g, size_t* bytes);
 /* Bind caller-owned device workspace (256-byte aligned) and upload the members' static tables
  * (synchronous).  Drops a captured graph. */
 int tamm_group_bind_workspace(tamm_group* g, void* dev_ptr, size_t bytes);
-/* Select one kernel configuration for every class (-1 = each class's default: the least padding)
+/* Select one kernel configuration for every class (-1 = each class's default: the least estimated
+ * time)
  * and the persistent grid size (0 = every resident slot: compute units x workgroups of the
  * configuration that fit on one).  Requires re-binding (the workspace size does not depend on
  * the configuration). */

@@ -100,11 +100,11 @@ hipError_t launch_screen(const ScreenParams& p, hipStream_t s) {
 // Software pipeline with one barrier per chunk: LDS holds two chunk buffers.  While the MFMAs
 // of chunk c run from one buffer, the registers holding chunk c+1 (loaded during the previous
 // chunk's MFMAs) are stored into the other buffer, the global loads of chunk c+2 are issued into
-// the same registers, and the offset-table entries of chunk c+3 are fetched.  Inside a chunk the
-// MFMA operands of k-step s+1 are read from LDS while the MFMAs of step s run.  In a tile inside
-// its block every MFMA block runs (padding k positions hold zeros) and the MFMA stream has no
-// branches; a tile that runs past its block deals its live output fragments over the waves
-// (see below).
+// the same registers, and the offset-table entries of chunk c+3 are fetched; these and the operand
+// reads of k-step s+1 are spread between the products of step s, and the barrier comes before the
+// last step's.  A tile takes the body compiled for its own number of 16 x 16 fragments per wave
+// (the planner cuts a block into tiles of even size), so no branch sits in the MFMA stream and no
+// fragment past a block's end is multiplied.
 //
 // v_mfma_f64_16x16x4_f64 lane layout (gfx950, checked on the device): A[m][k] comes from lane
 // m + 16k, B[k][n] from lane n + 16k, and D[m][n] lands in lane n + 16*(m%4), register m/4.
@@ -114,7 +114,8 @@ hipError_t launch_screen(const ScreenParams& p, hipStream_t s) {
 // workspace and k_reduce sums them in split order.  Results are bitwise reproducible.
 //
 // Launch modes: one workgroup per work item, or a persistent grid whose workgroups take items
-// from a counter (the grouped launch); the item order is the plan's.  The operands' gather
+// from the queue of the die they run on (long items, queue_pays in the planner); the item order is
+// the plan's.  The operands' gather
 // layouts (A_KC, B_KC) are template parameters: "layout" = 2*A_KC + B_KC.
 // ---------------------------------------------------------------------------------------------
 // LDS layout of one operand chunk (ROWS rows x KT summed indices, float64), chosen by the LDS's
