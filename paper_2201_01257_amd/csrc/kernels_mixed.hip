@@ -804,12 +804,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_contract_bf16s(ContractParam
 // configurations and dispatch
 // ---------------------------------------------------------------------------------------------
 static const MixedConfig kF32Configs[] = {
-    {64, 64, 16, 2, 2, 4, 84, 84, "f32_m64n64k16_w2x2"},
-    {128, 64, 16, 2, 2, 2, 90, 90, "f32_m128n64k16_w2x2"},
-    {64, 128, 16, 2, 2, 2, 90, 90, "f32_m64n128k16_w2x2"},
+    {64, 64, 16, 2, 2, 4, 86, 86, "f32_m64n64k16_w2x2"},
+    {128, 64, 16, 2, 2, 2, 93, 93, "f32_m128n64k16_w2x2"},
+    {64, 128, 16, 2, 2, 2, 92, 92, "f32_m64n128k16_w2x2"},
     {128, 128, 16, 2, 2, 1, 83, 83, "f32_m128n128k16_w2x2"},
-    {128, 128, 16, 4, 2, 1, 99, 99, "f32_m128n128k16_w4x2"},
-    {128, 128, 16, 2, 4, 1, 99, 99, "f32_m128n128k16_w2x4"},
+    {128, 128, 16, 4, 2, 1, 95, 95, "f32_m128n128k16_w4x2"},
+    {128, 128, 16, 2, 4, 1, 95, 95, "f32_m128n128k16_w2x4"},
 };
 // Eight waves where one workgroup fills a compute unit's LDS (two waves per SIMD): four on the same
 // tile were slower on both layouts (aligned ladder at O=24, V=104 1.04 against 0.88 ms; at O=64,

@@ -614,12 +614,12 @@ static int block_splits(int k_splits, double kext, double max_kext) {
 // were fitted to 108 contractions (3 kF to 6 TF, tiles of 3 to 64) timed with every configuration and
 // 1 to 16 K splits: taking the configuration with the least estimate costs 4 % against the best one
 // of each on average (up to 20 %), the rule before it (largest tile, no padding, two tiles per
-// compute unit) 14 % (up to 63 %).  The reduced precisions share them but for the tail, which the
-// dispatcher's rotation makes longer than the queues do; over 26 contractions in each of them the
-// least estimate costs 2-4 %, the rule before it 15 % in float32 and 20-40 % in split bfloat16, which
-// it ran on four-wave tiles.
+// compute unit) 14 % (up to 63 %).  The reduced precisions share them but for split bfloat16's
+// tail, whose few large workgroups leave more of it; over 26 contractions in each of them the least
+// estimate costs 2-3 %, the rule before it 15 % in float32 and 20-40 % in split bfloat16, which it ran
+// on four-wave tiles.
 constexpr double kRoundTrip16 = 0.60, kRoundTrip32 = 0.70, kRoundTripWave = 0.78;  // a chunk of 16, of 32, of a one-wave workgroup
-constexpr double kPair = 0.137, kItem = 3.84, kPer1024 = 0.63, kTail = 0.42, kTailMixed = 0.7, kGroupTail = 0.3;
+constexpr double kPair = 0.137, kItem = 3.84, kPer1024 = 0.63, kTail = 0.42, kTailSplit = 0.7, kGroupTail = 0.3;
 constexpr double kReduce = 5.6, kReduceBytes = 5.0e6;  // launch, bytes per microsecond
 
 static double item_us(const BlockShape& b, const TileCfg& f, double area, double parts) {
@@ -707,7 +707,7 @@ static double group_estimate_us(const std::vector<BlockShape>& shapes, const Til
 // estimated to gain 3 %, and in float64 8 % above a millisecond, where the queues have filled the tail
 // that splits would (ladder and its gradients at O=32, V=160: 3.1 ms in one part, 3.4 in four).  The partial tiles take at most an eighth of the tensors' bytes or 64 MiB.
 static std::pair<int, int> default_work(const tamm_plan* p, int config, int k_splits) {
-  const bool f64 = p->prec == TAMM_PREC_F64;
+  const bool f64 = p->prec == TAMM_PREC_F64, split_bf16 = !f64 && p->prec != TAMM_PREC_F32;
   const double bytes = p->stats.algorithmic_bytes, budget = std::max(bytes / 8, (double)(64 << 20));
   double best = 1e300, max_kext = 0;
   std::pair<int, int> pick(std::max(config, 0), std::max(k_splits, 1));
@@ -726,7 +726,7 @@ static std::pair<int, int> default_work(const tamm_plan* p, int config, int k_sp
         if (ns > 1) need += 8.0 * f.mt * f.nt * ns * (double)(((b.mext + f.mt - 1) / f.mt) * ((b.next + f.nt - 1) / f.nt) * b.count);
       }
       if (k_splits <= 0 && need > budget) continue;
-      const double t = estimate_us(p->shapes, f, splits, bytes, f64 ? kTail : kTailMixed);
+      const double t = estimate_us(p->shapes, f, splits, bytes, split_bf16 ? kTailSplit : kTail);
       if (t < least) {
         least = t;
         at = c;
