@@ -286,7 +286,7 @@ struct ChunkWalk {
   }
 };
 
-// Chunk pipeline of one work item, shared by the contraction kernels.  LDS holds two chunk
+// Chunk pipeline of one work item of the packed split-bfloat16 kernel.  LDS holds two chunk
 // buffers and there is one barrier per chunk: while compute(buf, ...) runs the MFMAs of chunk c
 // from buffer `buf`, the stage() callback it calls after its first k-step stores chunk c+1 (in
 // registers since the previous chunk) into the other buffer and issues the global loads of

@@ -480,7 +480,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MT * NT <= 64 * 64 ? 4 : WGM * WGN 
 // 16-byte LDS store.  The planner uses this layout only when every operand block's K extent is a
 // multiple of 8, so a group of 8 is either inside the block or wholly past its K extent; groups
 // past the rows or the K extent read zeros (offset beyond the buffer resource).
-// Same interface as Gather, for chunk_pipeline.
+// Same interface as Gather, for ChunkWalk.
 // ---------------------------------------------------------------------------------------------
 // LDS layout of a chunk in the planes layout: per plane, the 16-byte units (8 k of one row) are
 // stored k-group major, unit (k-group q, row r) at q*ROWS + (r ^ 2q).  An MFMA operand read (16
