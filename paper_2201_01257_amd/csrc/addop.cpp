@@ -173,14 +173,16 @@ bool add_chain_accepts(const tamm_add* head, const tamm_add* b, int* ydim) {
 
 // Work items of a chain: whole planes of out's last two dimensions when ydim is the
 // second-to-last, every block's plane holds at most kAddPlaneMax elements and lies contiguous in
-// every member's input (*plane = true); otherwise 32 x 32 tiles of the (ydim, last) plane.
-int add_chain_items(const std::vector<const tamm_add*>& m, int ydim, std::vector<AddItem>& items, bool* plane) {
+// every member's input (*plane = elements of the largest, else 0); otherwise 32 x 32 tiles of the (ydim, last) plane.
+int add_chain_items(const std::vector<const tamm_add*>& m, int ydim, std::vector<AddItem>& items, int32_t* plane) {
   const tamm_add* head = m[0];
   const int r = head->out->rank;
   bool pl = ydim == r - 2;
+  int32_t largest = 1;
   for (size_t b = 0; b < head->blocks.size() && pl; ++b) {
     const int ey = head->blocks[b].ext[r - 2], ex = head->blocks[b].ext[r - 1];
     if ((int64_t)ey * ex > kAddPlaneMax) pl = false;
+    else largest = std::max(largest, ey * ex);
     for (const tamm_add* a : m) {
       const AddBlock& B = a->blocks[b];
       const bool contiguous = a->ydim < 0 ? (B.istr[r - 1] == 1 && B.istr[r - 2] == ex)
@@ -188,7 +190,7 @@ int add_chain_items(const std::vector<const tamm_add*>& m, int ydim, std::vector
       pl = pl && contiguous;
     }
   }
-  *plane = pl;
+  *plane = pl ? largest : 0;
   items.clear();
   for (size_t b = 0; b < head->blocks.size(); ++b) {
     const AddBlock& B = head->blocks[b];
@@ -211,7 +213,7 @@ int add_chain_items(const std::vector<const tamm_add*>& m, int ydim, std::vector
 
 // Enqueue a chain: out = beta*out + sum_t alpha[t]*in_t (items from add_chain_items, on device).
 int add_chain_enqueue(const std::vector<tamm_add*>& m, const std::vector<double>& alpha, double beta, int ydim,
-                      bool plane, const AddItem* items, int64_t n_items, hipStream_t s) {
+                      int32_t plane, const AddItem* items, int64_t n_items, hipStream_t s) {
   if (m.empty() || m.size() > (size_t)kMaxAddTerms || alpha.size() != m.size())
     return fail(TAMM_ERR_ARG, "an AddOp chain has 1 to %d members", kMaxAddTerms);
   AddMultiParams p{};
@@ -236,7 +238,7 @@ int add_chain_enqueue(const std::vector<tamm_add*>& m, const std::vector<double>
   p.rank = m[0]->out->rank;
   p.ydim = ydim;
   p.nterms = (int32_t)m.size();
-  p.plane = plane ? 1 : 0;
+  p.plane = plane;
   if (plane && ydim != p.rank - 2) return fail(TAMM_ERR_ARG, "plane mode needs the last two dimensions");
   HIP_TRY(launch_add_multi(p, s));
   return TAMM_OK;

@@ -216,8 +216,8 @@ hipError_t launch_add(const AddParams& p, hipStream_t s);
 // sum_t alpha_t*in_t(permuted), out read and written once.  Every term shares out's block list
 // (blocks[t][b] describes out block b for term t).  trans[t] = 1 when in_t's last label is out
 // dimension ydim (read through LDS), 0 when it is out's last label (read directly).  Items are
-// transpose-mode tiles of the (ydim, last) plane, or, with plane = 1 (ydim = rank - 2, every
-// input's last two labels are out's last two, planes of at most kAddPlaneMax elements), whole
+// transpose-mode tiles of the (ydim, last) plane, or, with plane > 0 (ydim = rank - 2, every
+// input's last two labels are out's last two, planes of at most plane <= kAddPlaneMax elements), whole
 // planes: block and batch index over the other dimensions.
 constexpr int kMaxAddTerms = 8;
 constexpr int kAddPlaneMax = 1024;

@@ -246,49 +246,59 @@ __global__ __launch_bounds__(256) void k_add_multi(AddMultiParams P) {
   }
 }
 
-// Plane mode of the AddOp chain (small planes, contiguous in every input): one workgroup per
-// plane, lanes along the flattened plane, so a direct term is one contiguous run of loads; a
-// transposed term (its plane stored [x][y]) is read contiguously too and turned through LDS,
-// stored with a row stride of ey + 1 doubles so that the transposed reads spread over the banks.
+// Plane mode of the AddOp chain (small planes, contiguous in every input): LANES threads per plane
+// (64 for planes of at most 256 elements, four planes per workgroup; else all 256), lanes along the
+// flattened plane, so a direct term is one contiguous run of loads; a transposed term (its plane
+// stored [x][y]) is read contiguously too and turned through LDS, stored with a row stride of ey + 1
+// doubles so that the transposed reads spread over the banks.
+//
+// A workgroup lives for its dependent loads, so there are as few in a row as can be: item, the terms'
+// block descriptors (all at once), data (all at once).  The doubles residual's eight terms at O=27, V=81
+// in tiles of 8 and 12 (planes of at most 64 elements): 246 -> 55 us; at O=40, V=200 in tiles of 40
+// (planes of 400): 396 -> 397, HBM-bound.
+template <int LANES>
 __global__ __launch_bounds__(256) void k_add_multi_plane(AddMultiParams P) {
 #pragma clang fp contract(off)  // every product and every sum rounded once, as AddOps one by one
-  __shared__ double tile[2 * kAddPlaneMax];
-  const int64_t it = blockIdx.x;
-  if (it >= P.n_items) return;
-  const AddItem item = P.items[it];
+  constexpr int kPasses = 4, kPlanes = 256 / LANES, kMax = kPasses * LANES;
+  static_assert(kPasses * 256 == kAddPlaneMax, "four passes hold the largest plane");
+  __shared__ double tiles[kPlanes][2 * kMax];
+  const int lane = (int)threadIdx.x % LANES, plane = (int)threadIdx.x / LANES;
+  double* const tile = tiles[plane];
+  const int64_t it = (int64_t)blockIdx.x * kPlanes + plane;
+  const bool live = it < P.n_items;  // the others follow through the barriers and store nothing
+  const AddItem item = P.items[live ? it : P.n_items - 1];
   const int r = P.rank, yd = r - 2, xd = r - 1;
   const AddBlock& B0 = P.blocks[0][item.block];
-  const int ey = B0.ext[yd], ex = B0.ext[xd], n = ey * ex;
-  int idx[kMaxRank];
-  int rem = item.a;
-  for (int d = r - 3; d >= 0; --d) {
-    idx[d] = rem % B0.ext[d];
-    rem /= B0.ext[d];
-  }
-  const int64_t obase = B0.out_off + (int64_t)item.a * n;  // the plane is out's last two dimensions
-  constexpr int kPasses = kAddPlaneMax / 256;
-  double v[kMaxAddTerms][kPasses];
+  const int ey = B0.ext[yd], ex = B0.ext[xd], n = live ? ey * ex : 0;
+  // every term's plane: the offset of its block, then its strides times the batch index
+  const double* in[kMaxAddTerms];
+  bool stored[kMaxAddTerms];
 #pragma unroll
   for (int t = 0; t < kMaxAddTerms; ++t) {
+    const int64_t off = P.blocks[t < P.nterms ? t : 0][item.block].in_off;
+    stored[t] = t < P.nterms && off >= 0;  // a block not stored in a term's input adds zero
+    in[t] = P.in[t < P.nterms ? t : 0] + off;
+  }
+  int rem = item.a;
+  for (int d = r - 3; d >= 0; --d) {
+    const int ext = B0.ext[d], i = rem % ext;
+    rem /= ext;
 #pragma unroll
-    for (int q = 0; q < kPasses; ++q) v[t][q] = 0.0;
-    if (t >= P.nterms) continue;
-    const AddBlock& B = P.blocks[t][item.block];
-    if (B.in_off < 0) continue;  // block not stored in this term's input: adds zero
-    int64_t ibase = B.in_off;
-    for (int d = 0; d < r - 2; ++d) ibase += (int64_t)idx[d] * B.istr[d];
-    const double* __restrict__ in = P.in[t] + ibase;
+    for (int t = 0; t < kMaxAddTerms; ++t) in[t] += (int64_t)i * P.blocks[t < P.nterms ? t : 0][item.block].istr[d];
+  }
+  double* __restrict__ out = P.out + B0.out_off + (int64_t)item.a * (ey * ex);  // out's last two dimensions
+  double v[kMaxAddTerms][kPasses], acc[kPasses];
+#pragma unroll
+  for (int t = 0; t < kMaxAddTerms; ++t)
 #pragma unroll
     for (int q = 0; q < kPasses; ++q) {
-      const int f = (int)threadIdx.x + 256 * q;
-      if (f < n) v[t][q] = in[f];
+      const int f = lane + LANES * q;
+      v[t][q] = (stored[t] && f < n) ? in[t][f] : 0.0;
     }
-  }
-  double acc[kPasses];
 #pragma unroll
   for (int q = 0; q < kPasses; ++q) {
-    const int f = (int)threadIdx.x + 256 * q;
-    acc[q] = (P.beta != 0.0 && f < n) ? P.beta * P.out[obase + f] : 0.0;
+    const int f = lane + LANES * q;
+    acc[q] = (P.beta != 0.0 && f < n) ? P.beta * out[f] : 0.0;
   }
 #pragma unroll
   for (int t = 0; t < kMaxAddTerms; ++t) {
@@ -297,7 +307,7 @@ __global__ __launch_bounds__(256) void k_add_multi_plane(AddMultiParams P) {
       __syncthreads();  // the previous term's reads of the tile are done
 #pragma unroll
       for (int q = 0; q < kPasses; ++q) {
-        const int f = (int)threadIdx.x + 256 * q;  // in's plane index: f = x*ey + y
+        const int f = lane + LANES * q;  // in's plane index: f = x*ey + y
         if (f < n) {
           const int x = f / ey, y = f - x * ey;
           tile[x * (ey + 1) + y] = v[t][q];
@@ -306,7 +316,7 @@ __global__ __launch_bounds__(256) void k_add_multi_plane(AddMultiParams P) {
       __syncthreads();
 #pragma unroll
       for (int q = 0; q < kPasses; ++q) {
-        const int f = (int)threadIdx.x + 256 * q;  // out's plane index: f = y*ex + x
+        const int f = lane + LANES * q;  // out's plane index: f = y*ex + x
         if (f < n) {
           const int y = f / ex, x = f - y * ex;
           v[t][q] = tile[x * (ey + 1) + y];
@@ -318,14 +328,15 @@ __global__ __launch_bounds__(256) void k_add_multi_plane(AddMultiParams P) {
   }
 #pragma unroll
   for (int q = 0; q < kPasses; ++q) {
-    const int f = (int)threadIdx.x + 256 * q;
-    if (f < n) P.out[obase + f] = acc[q];
+    const int f = lane + LANES * q;
+    if (f < n) out[f] = acc[q];
   }
 }
 
 hipError_t launch_add_multi(const AddMultiParams& p, hipStream_t s) {
   if (p.n_items <= 0) return hipSuccess;
-  if (p.plane) hipLaunchKernelGGL(k_add_multi_plane, dim3((unsigned)p.n_items), dim3(256), 0, s, p);
+  if (p.plane > 256) hipLaunchKernelGGL(k_add_multi_plane<256>, dim3((unsigned)p.n_items), dim3(256), 0, s, p);
+  else if (p.plane > 0) hipLaunchKernelGGL(k_add_multi_plane<64>, dim3((unsigned)((p.n_items + 3) / 4)), dim3(256), 0, s, p);
   else hipLaunchKernelGGL(k_add_multi, dim3((unsigned)p.n_items), dim3(256), 0, s, p);
   return hipGetLastError();
 }

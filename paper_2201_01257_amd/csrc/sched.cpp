@@ -35,7 +35,7 @@ struct Node {
   std::vector<int> ops;  // queued operations, in queue order (several: a fused contraction or AddOp chain)
   int level = -1;
   int add_ydim = -1;               // AddOp chain: out dimension of its transposed terms' last label
-  bool add_plane = false;          // AddOp chain: whole planes per work item
+  int32_t add_plane = 0;          // AddOp chain: whole planes per work item
   std::vector<AddItem> add_items;  // AddOp chain: work items, uploaded at bind time
   size_t items_off = 0;
 };
