@@ -254,7 +254,10 @@ int tamm_plan_autotune_workspace_size(const tamm_plan* p, size_t* bytes);
 int tamm_plan_autotune(tamm_plan* p, void* workspace, size_t bytes, void* stream, const char* cache_path, int32_t reps);
 
 /* Enqueue the whole operation on stream: tamm_plan_screen then tamm_plan_contract.
- * Requires bound storage on all three tensors and a bound workspace. */
+ * Requires bound storage on all three tensors and a bound workspace.  Executions of one plan may
+ * overlap (on several streams or in captured graphs, out bound to other storage in between), except
+ * of a plan with K splits or of a split-bfloat16 precision: their partial sums and operand copies
+ * are in the plan's one workspace, so the caller orders them. */
 int tamm_plan_execute(tamm_plan* p, double alpha, double beta, void* stream);
 
 /* The two halves of tamm_plan_execute.  tamm_plan_screen enqueues the GPU tile-pair screening,

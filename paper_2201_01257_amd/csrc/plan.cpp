@@ -112,6 +112,53 @@ void merge_shapes(std::vector<BlockShape>& v) {
   v.resize(n);
 }
 
+// Counter sets of a plan's persistent launches, in its workspace.  Two launches that overlap must
+// not share one: the later one's clearing would hand items of the earlier one out again.  Eager
+// launches take the first kEagerSets in turn, each after the last launch on its set (an event, so
+// that any stream may come next).  A captured launch replays with its set whenever the graph runs, so
+// it gets one of the others for good; when those are used up it runs as a plain launch.
+constexpr int kEagerSets = 8, kCapturedSets = 24;
+struct QueueSets {
+  std::mutex mu;                     // launches of one plan from several threads
+  hipEvent_t done[kEagerSets] = {};  // end of the last eager launch on the set
+  int device = -1;                   // of the events
+  int next = 0, captured = 0;
+
+  ~QueueSets() { drop_events(); }
+  void drop_events() {
+    for (hipEvent_t& e : done) {
+      if (e) (void)hipEventDestroy(e);
+      e = nullptr;
+    }
+  }
+  // The set of a launch on s, which may run when s gets there; -1: none is left.
+  int take(hipStream_t s, int* set) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) != hipSuccess) {
+      (void)hipGetLastError();
+      *set = -1;
+      return TAMM_OK;
+    }
+    if (status != hipStreamCaptureStatusNone) {
+      *set = captured < kCapturedSets ? kEagerSets + captured++ : -1;
+      return TAMM_OK;
+    }
+    int dev = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    if (dev != device) drop_events();  // the workspace moved to another device
+    device = dev;
+    *set = next;
+    next = (next + 1) % kEagerSets;
+    if (done[*set]) HIP_TRY(hipStreamWaitEvent(s, done[*set], 0));
+    else HIP_TRY(hipEventCreateWithFlags(&done[*set], hipEventDisableTiming));
+    return TAMM_OK;
+  }
+  int launched(int set, hipStream_t s) {
+    if (set >= 0 && set < kEagerSets) HIP_TRY(hipEventRecord(done[set], s));
+    return TAMM_OK;
+  }
+};
+
 }  // namespace
 
 struct tamm_plan {
@@ -153,7 +200,7 @@ struct tamm_plan {
   bool queued = false;             // persistent launch over the dies' queues (float64, more items than resident workgroups)
   bool no_queue = false;           // never (tamm_contract_noalloc keeps its workspace as small as it was)
   int32_t queue_begin[kQueues + 1] = {};
-  int queue_slot = 0;              // counter set of the next launch, round robin
+  QueueSets sets;
   std::vector<ReduceItem> reduce;
   tamm_plan_stats stats{};
   // workspace: static layout, then work list, reduce list, partial tiles
@@ -175,7 +222,6 @@ static int gather_layout(const tamm_plan* p) {
 }
 constexpr int kLayouts = 8;
 constexpr int kComputeUnits = 256;  // MI355X
-constexpr int kQueueSlots = 8;      // counter sets of a plan's persistent launches
 
 static Layout make_layout(const tamm_plan* p, size_t base) {
   Layout L;
@@ -828,7 +874,7 @@ static void layout_workspace(tamm_plan* p, const TileCfg& f, size_t items, size_
   p->off_reduce = off;
   off = align256(off + reduces * sizeof(ReduceItem));
   p->off_queue = off;
-  if (queued) off = align256(off + kQueueSlots * kQueues * sizeof(int32_t));
+  if (queued) off = align256(off + (kEagerSets + kCapturedSets) * kQueues * sizeof(int32_t));
   p->off_partial = off;
   if (partials > 0) off = align256(off + partials * f.mt * f.nt * sizeof(double));
   if (p->prec == TAMM_PREC_BF16X3 || p->prec == TAMM_PREC_BF16X4_ALIGNED) {
@@ -1099,16 +1145,23 @@ static int contract_launch(tamm_plan* p, double alpha, double beta, hipStream_t 
   cp.n_work = (int32_t)p->work.size();
   const int layout = gather_layout(p);
   if (p->prec == TAMM_PREC_F64) {
-    int grid = 0;
     if (p->queued) {
-      // launches of one plan on different streams take counter sets of their own
-      cp.queue_next = (int32_t*)(p->ws + p->off_queue) + p->queue_slot * kQueues;
-      p->queue_slot = (p->queue_slot + 1) % kQueueSlots;
-      std::copy(p->queue_begin, p->queue_begin + kQueues + 1, cp.queue_begin);
-      grid = persistent_grid(p->config, layout, cp.n_work);
-      HIP_TRY(launch_clear_queues(cp.queue_next, s));
+      std::lock_guard<std::mutex> lock(p->sets.mu);
+      int set = -1, grid = 0;
+      int rc = p->sets.take(s, &set);
+      if (rc != TAMM_OK) return rc;
+      if (set >= 0) {
+        cp.queue_next = (int32_t*)(p->ws + p->off_queue) + set * kQueues;
+        std::copy(p->queue_begin, p->queue_begin + kQueues + 1, cp.queue_begin);
+        grid = persistent_grid(p->config, layout, cp.n_work);
+        HIP_TRY(launch_clear_queues(cp.queue_next, s));
+      }
+      HIP_TRY(launch_contract_f64(p->config, layout, cp, grid, s));
+      rc = p->sets.launched(set, s);
+      if (rc != TAMM_OK) return rc;
+    } else {
+      HIP_TRY(launch_contract_f64(p->config, layout, cp, 0, s));
     }
-    HIP_TRY(launch_contract_f64(p->config, layout, cp, grid, s));
   } else {
     if (p->prec != TAMM_PREC_F32) {
       // operand split into packed bfloat16 slices, then the contraction reads the split copies

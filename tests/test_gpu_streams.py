@@ -1,0 +1,66 @@
+"""Launches of one plan that overlap: on more streams than the plan has counter sets, and in captured
+graphs (more of them than there are sets for) beside eager launches, each with an output of its own.
+Every output must hold the bits that the plan writes alone."""
+
+import pytest
+import torch
+
+from paper_2201_01257_amd import core as tm
+
+pytestmark = pytest.mark.gpu
+
+
+def queued_plan():
+    # 576 tiles of 128 x 128, about 60 us each: more items than resident workgroups, long enough for the queues
+    m, k = tm.Space.explicit([1500, 1500]), tm.Space.explicit([200, 56])
+    A, B, C = tm.Tensor([m, k]), tm.Tensor([k, m]), tm.Tensor([m, m])
+    g = torch.Generator(device="cuda").manual_seed(11)
+    for t in (A, B):
+        t.data.copy_(torch.randn(t.data.shape, dtype=torch.float64, device="cuda", generator=g))
+    plan = tm.Plan(C, "ij", A, "ik", B, "kj")
+    plan.set_config(3, 1)
+    plan.execute(1.0, 0.0)
+    torch.cuda.synchronize()
+    want = C.data.clone()
+    ref = A.to_dense() @ B.to_dense()
+    assert abs(C.to_dense() - ref).max() <= 1e-11 * abs(ref).max()
+    return plan, C, want
+
+
+def test_launches_on_more_streams_than_counter_sets():
+    plan, C, want = queued_plan()
+    streams = [torch.cuda.Stream() for _ in range(12)]
+    outs = [torch.full_like(want, float("nan")) for _ in range(36)]
+    torch.cuda.synchronize()
+    for i, out in enumerate(outs):
+        C.bind(out)
+        plan.execute(1.0, 0.0, stream=streams[i % 12].cuda_stream)
+    torch.cuda.synchronize()
+    for i, out in enumerate(outs):
+        assert torch.equal(out, want), i
+
+
+def test_captured_launches_beside_eager_ones():
+    plan, C, want = queued_plan()
+    outs = [torch.full_like(want, float("nan")) for _ in range(30)]
+    graphs = []
+    for out in outs[:26]:  # two more than there are sets for captured launches
+        C.bind(out)
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            plan.execute(1.0, 0.0)
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    for _ in range(2):
+        for out in outs:
+            out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for i, out in enumerate(outs):
+            with torch.cuda.stream(streams[i % 4]):
+                if i < len(graphs):
+                    graphs[i].replay()
+                else:
+                    C.bind(out)
+                    plan.execute(1.0, 0.0)
+        torch.cuda.synchronize()
+        for i, out in enumerate(outs):
+            assert torch.equal(out, want), i
