@@ -367,7 +367,7 @@ int tamm_group_set_config(tamm_group* g, int32_t config, int32_t grid);
  * launches may still read the old descriptors); calls with unchanged values launch
  * asynchronously. */
 int tamm_group_execute(tamm_group* g, const double* alpha, const double* beta, void* stream);
-/* Capture the group's launches (counter reset, screening, persistent contraction; no memset or
+/* Capture the group's launches (screening, which clears the queue counters, and contractions; no memset or
  * copy nodes) into a hipGraph on an internal stream, with alpha/beta fixed at these values;
  * later tamm_group_execute calls with the same values replay it on their stream. */
 int tamm_group_capture(tamm_group* g, const double* alpha, const double* beta, void* stream);

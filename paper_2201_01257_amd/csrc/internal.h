@@ -143,8 +143,9 @@ struct ScreenParams {
   const ScreenDesc* probs;       // group: per-problem screen descriptors
   const int32_t* item_prob;      // group: problem of each screening item
   const int32_t* item_block;     // group: output block of each screening item
+  int32_t* queue_next;           // n_queues counters to clear for the contraction that follows
   int32_t n_items;               // single: = single.n_blocks
-  int32_t pad;
+  int32_t n_queues;
 };
 
 struct ReduceItem {

@@ -30,6 +30,7 @@ __global__ __launch_bounds__(64) void k_screen(ScreenParams P) {
   const ScreenDesc* S = P.probs ? P.probs + P.item_prob[item] : &P.single;
   const int ob = P.probs ? P.item_block[item] : item;
   const int lane = threadIdx.x;
+  if (item == 0 && lane < P.n_queues) P.queue_next[lane] = 0;
   PairDesc* __restrict__ out = S->pairs + (int64_t)ob * S->pair_stride;
   int32_t* counts = S->counts;
   int count = 0;

@@ -200,6 +200,7 @@ struct tamm_plan {
   bool queued = false;             // persistent launch over the dies' queues (float64, more items than resident workgroups)
   bool no_queue = false;           // never (tamm_contract_noalloc keeps its workspace as small as it was)
   int32_t queue_begin[kQueues + 1] = {};
+  int queue_grid = 0;              // workgroups of a persistent launch on the device it is bound on
   QueueSets sets;
   std::vector<ReduceItem> reduce;
   tamm_plan_stats stats{};
@@ -1021,6 +1022,17 @@ extern "C" int tamm_plan_workspace_size(const tamm_plan* p, size_t* bytes) {
   return ok();
 }
 
+// Workgroups of a persistent launch: every resident slot of the device (compute units x resident
+// workgroups of the configuration), at most one per item.
+static int persistent_grid(int config, int layout, int n_work) {
+  int dev = 0, cus = kComputeUnits;
+  if (hipGetDevice(&dev) == hipSuccess) {
+    int v = 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
+  }
+  return std::max(1, std::min<int>(f64_occupancy(config, layout) * cus, n_work));
+}
+
 static int bind_plan(tamm_plan* p, void* dev_ptr, size_t bytes) {
   if (!dev_ptr || ((uintptr_t)dev_ptr) % 256) return fail(TAMM_ERR_WORKSPACE, "workspace must be non-null and 256-byte aligned");
   if (bytes < p->ws_size) return fail(TAMM_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu needed", bytes, p->ws_size);
@@ -1032,6 +1044,7 @@ static int bind_plan(tamm_plan* p, void* dev_ptr, size_t bytes) {
     HIP_TRY(hipMemcpy(ws + p->off_reduce, p->reduce.data(), p->reduce.size() * sizeof(ReduceItem), hipMemcpyHostToDevice));
   if (!p->prepA.empty()) HIP_TRY(hipMemcpy(ws + p->off_prepA, p->prepA.data(), p->prepA.size() * sizeof(PrepBlock), hipMemcpyHostToDevice));
   if (!p->prepB.empty()) HIP_TRY(hipMemcpy(ws + p->off_prepB, p->prepB.data(), p->prepB.size() * sizeof(PrepBlock), hipMemcpyHostToDevice));
+  if (p->queued) p->queue_grid = persistent_grid(p->config, gather_layout(p), (int)p->work.size());
   p->ws = ws;
   p->ws_bytes = bytes;
   p->ws_bound = true;
@@ -1113,30 +1126,41 @@ static int check_bound(const tamm_plan* p) {
   return check_tensors(p);
 }
 
-extern "C" int tamm_plan_screen(tamm_plan* p, void* stream) {
-  if (!p) return fail(TAMM_ERR_ARG, "null plan");
-  int rc = check_bound(p);
-  if (rc != TAMM_OK) return rc;
+static int screen_launch(tamm_plan* p, int32_t* queue_next, hipStream_t s) {
   ScreenParams sp{};
   sp.single = screen_desc(p, p->ws, p->lay);
   sp.n_items = sp.single.n_blocks;
-  HIP_TRY(launch_screen(sp, (hipStream_t)stream));
+  sp.queue_next = queue_next;
+  sp.n_queues = queue_next ? kQueues : 0;
+  HIP_TRY(launch_screen(sp, s));
   p->screened = true;
-  return ok();
+  return TAMM_OK;
 }
 
-// Workgroups of a persistent launch: every resident slot of the device (compute units x resident
-// workgroups of the configuration), at most one per item.
-static int persistent_grid(int config, int layout, int n_work) {
-  int dev = 0, cus = kComputeUnits;
-  if (hipGetDevice(&dev) == hipSuccess) {
-    int v = 0;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
+extern "C" int tamm_plan_screen(tamm_plan* p, void* stream) {
+  if (!p) return fail(TAMM_ERR_ARG, "null plan");
+  int rc = check_bound(p);
+  if (rc == TAMM_OK) rc = screen_launch(p, nullptr, (hipStream_t)stream);
+  return rc == TAMM_OK ? ok() : rc;
+}
+
+// The persistent launch of long items, after the screening if `screen` (which then clears its counters).
+static int queue_launch(tamm_plan* p, ContractParams& cp, int layout, bool screen, hipStream_t s) {
+  std::lock_guard<std::mutex> lock(p->sets.mu);
+  int set = -1;
+  int rc = p->sets.take(s, &set);
+  if (rc != TAMM_OK) return rc;
+  if (set >= 0) {
+    cp.queue_next = (int32_t*)(p->ws + p->off_queue) + set * kQueues;
+    std::copy(p->queue_begin, p->queue_begin + kQueues + 1, cp.queue_begin);
+    if (!screen) HIP_TRY(launch_clear_queues(cp.queue_next, s));
   }
-  return std::max(1, std::min<int>(f64_occupancy(config, layout) * cus, n_work));
+  if (screen && (rc = screen_launch(p, cp.queue_next, s)) != TAMM_OK) return rc;
+  HIP_TRY(launch_contract_f64(p->config, layout, cp, set >= 0 ? p->queue_grid : 0, s));
+  return p->sets.launched(set, s);
 }
 
-static int contract_launch(tamm_plan* p, double alpha, double beta, hipStream_t s) {
+static int contract_launch(tamm_plan* p, double alpha, double beta, bool screen, hipStream_t s) {
   ContractParams cp{};
   cp.single = problem_desc(p, p->ws, p->lay, p->k_splits > 1 ? (double*)(p->ws + p->off_partial) : nullptr, p->k_splits,
                            alpha, beta);
@@ -1144,20 +1168,13 @@ static int contract_launch(tamm_plan* p, double alpha, double beta, hipStream_t 
   cp.work = (const WorkItem*)(p->ws + p->off_work);
   cp.n_work = (int32_t)p->work.size();
   const int layout = gather_layout(p);
+  if (screen && !p->queued) {
+    const int rc = screen_launch(p, nullptr, s);
+    if (rc != TAMM_OK) return rc;
+  }
   if (p->prec == TAMM_PREC_F64) {
     if (p->queued) {
-      std::lock_guard<std::mutex> lock(p->sets.mu);
-      int set = -1, grid = 0;
-      int rc = p->sets.take(s, &set);
-      if (rc != TAMM_OK) return rc;
-      if (set >= 0) {
-        cp.queue_next = (int32_t*)(p->ws + p->off_queue) + set * kQueues;
-        std::copy(p->queue_begin, p->queue_begin + kQueues + 1, cp.queue_begin);
-        grid = persistent_grid(p->config, layout, cp.n_work);
-        HIP_TRY(launch_clear_queues(cp.queue_next, s));
-      }
-      HIP_TRY(launch_contract_f64(p->config, layout, cp, grid, s));
-      rc = p->sets.launched(set, s);
+      const int rc = queue_launch(p, cp, layout, screen, s);
       if (rc != TAMM_OK) return rc;
     } else {
       HIP_TRY(launch_contract_f64(p->config, layout, cp, 0, s));
@@ -1216,16 +1233,20 @@ extern "C" int tamm_plan_contract(tamm_plan* p, double alpha, double beta, void*
   int rc = check_bound(p);
   if (rc != TAMM_OK) return rc;
   if (!p->screened) return fail(TAMM_ERR_UNBOUND, "the plan has not been screened on its bound workspace");
-  rc = contract_launch(p, alpha, beta, (hipStream_t)stream);
+  rc = contract_launch(p, alpha, beta, false, (hipStream_t)stream);
   if (rc != TAMM_OK) return rc;
   p->executed = true;
   return ok();
 }
 
 extern "C" int tamm_plan_execute(tamm_plan* p, double alpha, double beta, void* stream) {
-  int rc = tamm_plan_screen(p, stream);
+  if (!p) return fail(TAMM_ERR_ARG, "null plan");
+  int rc = check_bound(p);
   if (rc != TAMM_OK) return rc;
-  return tamm_plan_contract(p, alpha, beta, stream);
+  rc = contract_launch(p, alpha, beta, true, (hipStream_t)stream);
+  if (rc != TAMM_OK) return rc;
+  p->executed = true;
+  return ok();
 }
 
 extern "C" int tamm_plan_screen_result(tamm_plan* p, void* stream, int32_t* counts, int32_t* k_tiles) {
@@ -1627,6 +1648,7 @@ struct tamm_group {
   size_t work_capacity = 0;         // work items of the largest mix of per-class configurations
   int32_t queue_begin[kLayouts][kQueues + 1] = {};  // each class's queues, relative to its work range
   bool queued[kLayouts] = {};            // a persistent launch pays (queue_pays)
+  int auto_grid[kLayouts] = {};          // its workgroups on the device the group is bound on
   int32_t cls_begin[kLayouts + 1] = {};  // work range of gather layout c: [cls_begin[c], cls_begin[c+1])
   int cfg[kLayouts] = {};   // kernel configuration of each layout class (its tile shape)
   int grid[kLayouts] = {};  // persistent grid of each layout class (0: automatic)
@@ -1966,6 +1988,10 @@ static int group_bind(tamm_group* g, void* dev_ptr, size_t bytes) {
   items.insert(items.end(), g->sitem_block.begin(), g->sitem_block.end());
   if (!items.empty()) HIP_TRY(hipMemcpy(ws + g->off_sitems, items.data(), items.size() * sizeof(int32_t), hipMemcpyHostToDevice));
   if (!g->work.empty()) HIP_TRY(hipMemcpy(ws + g->off_work, g->work.data(), g->work.size() * sizeof(WorkItem), hipMemcpyHostToDevice));
+  for (int c = 0; c < kLayouts; ++c) {
+    const int n = g->cls_begin[c + 1] - g->cls_begin[c];
+    g->auto_grid[c] = n > 0 && g->queued[c] ? persistent_grid(g->cfg[c], c, n) : 0;
+  }
   g->ws = ws;
   g->ws_bytes = bytes;
   g->bound = true;
@@ -1988,24 +2014,19 @@ extern "C" int tamm_group_set_config(tamm_group* g, int32_t config, int32_t grid
   return ok();
 }
 
-// Persistent grid of one layout class: the tuned size, else every resident slot of the device.
-static int group_grid(const tamm_group* g, int layout, int n_work) {
-  if (g->grid[layout] > 0) return std::max(1, std::min<int>(g->grid[layout], n_work));
-  return persistent_grid(g->cfg[layout], layout, n_work);
-}
-
-// The persistent contraction launch of one layout class (counter reset first); nothing for an
-// empty class.  Consumes the last screening results.
-static int group_enqueue_class(tamm_group* g, int c, hipStream_t s) {
+// The contraction launch of one layout class, persistent on the tuned grid or, for long items, on every
+// resident slot of the device; nothing for an empty class.  Consumes the last screening results;
+// `cleared`: the screening has just cleared the queue counters.
+static int group_enqueue_class(tamm_group* g, int c, bool cleared, hipStream_t s) {
   const int n = g->cls_begin[c + 1] - g->cls_begin[c];
   if (n <= 0) return TAMM_OK;
   ContractParams cp{};
   int grid = 0;
   if (g->grid[c] > 0 || g->queued[c]) {
-    grid = group_grid(g, c, n);
+    grid = g->grid[c] > 0 ? std::min<int>(g->grid[c], n) : g->auto_grid[c];
     cp.queue_next = (int32_t*)(g->ws + g->off_counter) + c * kQueues;
     std::copy(g->queue_begin[c], g->queue_begin[c] + kQueues + 1, cp.queue_begin);
-    HIP_TRY(launch_clear_queues(cp.queue_next, s));
+    if (!cleared) HIP_TRY(launch_clear_queues(cp.queue_next, s));
   }
   cp.probs = (const ProblemDesc*)(g->ws + g->off_pdesc);
   cp.work = (const WorkItem*)(g->ws + g->off_work) + g->cls_begin[c];
@@ -2016,7 +2037,7 @@ static int group_enqueue_class(tamm_group* g, int c, hipStream_t s) {
 
 namespace tamm {
 
-// Enqueue the group's kernels (screening, then per class a counter reset and the persistent
+// Enqueue the group's kernels (screening, which clears the queue counters, then each class's
 // contraction), consuming the descriptors in the workspace.
 int group_enqueue(tamm_group* g, hipStream_t s) {
   ScreenParams sp{};
@@ -2024,6 +2045,9 @@ int group_enqueue(tamm_group* g, hipStream_t s) {
   sp.item_prob = (const int32_t*)(g->ws + g->off_sitems);
   sp.item_block = sp.item_prob + g->sitem_prob.size();
   sp.n_items = (int32_t)g->sitem_prob.size();
+  sp.queue_next = (int32_t*)(g->ws + g->off_counter);
+  sp.n_queues = kLayouts * kQueues;
+  static_assert(kLayouts * kQueues <= 64, "one counter per lane of a screening workgroup");
   HIP_TRY(launch_screen(sp, s));
   // one persistent launch per gather layout present in the group.  With several, they run
   // concurrently: the first on the caller's stream, the others on side streams that wait for the
@@ -2039,7 +2063,7 @@ int group_enqueue(tamm_group* g, hipStream_t s) {
   }();
   if (np <= 1 || serial) {
     for (int i = 0; i < np; ++i) {
-      const int rc = group_enqueue_class(g, present[i], s);
+      const int rc = group_enqueue_class(g, present[i], true, s);
       if (rc != TAMM_OK) return rc;
     }
     return TAMM_OK;
@@ -2051,11 +2075,11 @@ int group_enqueue(tamm_group* g, hipStream_t s) {
     if (!g->side[c]) HIP_TRY(hipStreamCreateWithFlags(&g->side[c], hipStreamNonBlocking));
     if (!g->ev_join[c]) HIP_TRY(hipEventCreateWithFlags(&g->ev_join[c], hipEventDisableTiming));
     HIP_TRY(hipStreamWaitEvent(g->side[c], g->ev_fork, 0));
-    const int rc = group_enqueue_class(g, c, g->side[c]);
+    const int rc = group_enqueue_class(g, c, true, g->side[c]);
     if (rc != TAMM_OK) return rc;
     HIP_TRY(hipEventRecord(g->ev_join[c], g->side[c]));
   }
-  const int rc = group_enqueue_class(g, present[0], s);
+  const int rc = group_enqueue_class(g, present[0], true, s);
   if (rc != TAMM_OK) return rc;
   for (int i = 1; i < np; ++i) HIP_TRY(hipStreamWaitEvent(s, g->ev_join[present[i]], 0));
   return TAMM_OK;
@@ -2220,7 +2244,7 @@ int group_autotune(tamm_group* g, hipStream_t s, const char* cache_path, int32_t
         for (int c = 0; c < kLayouts && rc == TAMM_OK; ++c) {
           if (g->cls_begin[c + 1] == g->cls_begin[c]) continue;
           HIP_TRY(hipEventRecord(e0, s));
-          for (int r = 0; r < reps && rc == TAMM_OK; ++r) rc = group_enqueue_class(g, c, s);
+          for (int r = 0; r < reps && rc == TAMM_OK; ++r) rc = group_enqueue_class(g, c, false, s);
           HIP_TRY(hipEventRecord(e1, s));
           HIP_TRY(hipEventSynchronize(e1));
           float ms = 0;

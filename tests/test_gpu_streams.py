@@ -64,3 +64,13 @@ def test_captured_launches_beside_eager_ones():
         torch.cuda.synchronize()
         for i, out in enumerate(outs):
             assert torch.equal(out, want), i
+
+
+def test_contractions_after_one_screening():
+    plan, C, want = queued_plan()
+    plan.screen()
+    for _ in range(3):  # no screening in between to clear the counters
+        C.data.fill_(float("nan"))
+        plan.contract(1.0, 0.0)
+        torch.cuda.synchronize()
+        assert torch.equal(C.data, want)
