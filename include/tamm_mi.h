@@ -255,9 +255,11 @@ int tamm_plan_autotune(tamm_plan* p, void* workspace, size_t bytes, void* stream
 
 /* Enqueue the whole operation on stream: tamm_plan_screen then tamm_plan_contract.
  * Requires bound storage on all three tensors and a bound workspace.  Executions of one plan may
- * overlap (on several streams or in captured graphs, out bound to other storage in between), except
- * of a plan with K splits or of a split-bfloat16 precision: their partial sums and operand copies
- * are in the plan's one workspace, so the caller orders them. */
+ * overlap (on several streams or in captured graphs, out bound to other storage in between) with two
+ * exceptions, in which the caller orders them: a split-bfloat16 plan keeps its operand copies in its
+ * one workspace, and a plan with K splits its partial sums (where the output has at least 512 tiles of
+ * 128 x 128, which fill the chip without splits, or its sums are short, the library orders the
+ * executions outside captured graphs by an event). */
 int tamm_plan_execute(tamm_plan* p, double alpha, double beta, void* stream);
 
 /* The two halves of tamm_plan_execute.  tamm_plan_screen enqueues the GPU tile-pair screening,

@@ -112,27 +112,28 @@ void merge_shapes(std::vector<BlockShape>& v) {
   v.resize(n);
 }
 
-// Counter sets of a plan's persistent launches, in its workspace.  Two launches that overlap must
-// not share one: the later one's clearing would hand items of the earlier one out again.  Eager
-// launches take the first kEagerSets in turn, each after the last launch on its set (an event, so
-// that any stream may come next).  A captured launch replays with its set whenever the graph runs, so
-// it gets one of the others for good; when those are used up it runs as a plain launch.
+// What launches of one plan share in its workspace, and how they are kept apart when they overlap.
+// Counter sets of persistent launches: the later one's clearing would hand items of the earlier one
+// out again.  Eager launches take the first kEagerSets in turn, each after the last launch on its set
+// (an event, so that any stream may come next).  A captured launch replays with its set whenever the
+// graph runs, so it gets one of the others for good; when those are used up it runs as a plain launch.
+// Partial sums, of which there is one set: eager launches come one after another (`serial`).
 constexpr int kEagerSets = 8, kCapturedSets = 24;
-struct QueueSets {
+struct SharedSets {
   std::mutex mu;                     // launches of one plan from several threads
   hipEvent_t done[kEagerSets] = {};  // end of the last eager launch on the set
   int device = -1;                   // of the events
   int next = 0, captured = 0;
 
-  ~QueueSets() { drop_events(); }
+  ~SharedSets() { drop_events(); }
   void drop_events() {
     for (hipEvent_t& e : done) {
       if (e) (void)hipEventDestroy(e);
       e = nullptr;
     }
   }
-  // The set of a launch on s, which may run when s gets there; -1: none is left.
-  int take(hipStream_t s, int* set) {
+  // The counter set of a launch on s, which may run when s gets there; -1: none is left.
+  int take(hipStream_t s, bool counters, bool serial, int* set) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &status) != hipSuccess) {
       (void)hipGetLastError();
@@ -140,15 +141,15 @@ struct QueueSets {
       return TAMM_OK;
     }
     if (status != hipStreamCaptureStatusNone) {
-      *set = captured < kCapturedSets ? kEagerSets + captured++ : -1;
+      *set = counters && captured < kCapturedSets ? kEagerSets + captured++ : -1;
       return TAMM_OK;
     }
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
     if (dev != device) drop_events();  // the workspace moved to another device
     device = dev;
-    *set = next;
-    next = (next + 1) % kEagerSets;
+    *set = serial ? 0 : next;
+    next = (*set + 1) % kEagerSets;
     if (done[*set]) HIP_TRY(hipStreamWaitEvent(s, done[*set], 0));
     else HIP_TRY(hipEventCreateWithFlags(&done[*set], hipEventDisableTiming));
     return TAMM_OK;
@@ -200,8 +201,9 @@ struct tamm_plan {
   bool queued = false;             // persistent launch over the dies' queues (float64, more items than resident workgroups)
   bool no_queue = false;           // never (tamm_contract_noalloc keeps its workspace as small as it was)
   int32_t queue_begin[kQueues + 1] = {};
+  bool serial = false;             // eager launches one after another: they share partial sums
   int queue_grid = 0;              // workgroups of a persistent launch on the device it is bound on
-  QueueSets sets;
+  SharedSets sets;
   std::vector<ReduceItem> reduce;
   tamm_plan_stats stats{};
   // workspace: static layout, then work list, reduce list, partial tiles
@@ -751,7 +753,9 @@ static double group_estimate_us(const std::vector<BlockShape>& shapes, const Til
 }
 
 // Default configuration and K splits of a plan: the least estimate; more splits only where they are
-// estimated to gain 3 %, and in float64 8 % above a millisecond, where the queues have filled the tail
+// estimated to gain 3 %, never of sums shorter than eight chunks in float64 and float32 (what they gain
+// is what ordering overlapping executions costs, see `starved`: ring at O=5, V=45 16 us in four parts,
+// 19 in one, 20 in four with the event; in split bfloat16 at O=9, V=37 35, 43 and 38), and in float64 8 % above a millisecond, where the queues have filled the tail
 // that splits would (ladder and its gradients at O=32, V=160: 3.1 ms in one part, 3.4 in four).  The partial tiles take at most an eighth of the tensors' bytes or 64 MiB.
 static std::pair<int, int> default_work(const tamm_plan* p, int config, int k_splits) {
   const bool f64 = p->prec == TAMM_PREC_F64, split_bf16 = !f64 && p->prec != TAMM_PREC_F32;
@@ -759,8 +763,9 @@ static std::pair<int, int> default_work(const tamm_plan* p, int config, int k_sp
   double best = 1e300, max_kext = 0;
   std::pair<int, int> pick(std::max(config, 0), std::max(k_splits, 1));
   for (const BlockShape& b : p->shapes) max_kext = std::max(max_kext, b.kext);
+  const bool short_sums = !split_bf16 && max_kext < 8 * 16;
   for (int ks : {1, 2, 4, 8, 16}) {
-    if (k_splits > 0 && ks > 1) break;
+    if (ks > 1 && (k_splits > 0 || short_sums)) break;
     const int splits = k_splits > 0 ? k_splits : ks;
     double least = 1e300;
     int at = -1;
@@ -926,6 +931,21 @@ size_t tamm::plan_candidate_workspace(const tamm_plan* p, int max_splits) {
   return most;
 }
 
+// An output of fewer than two 128 x 128 tiles per compute unit, and sums of eight chunks and more: only
+// K splits fill the chip, and executions that overlap are the caller's to order.  Other plans gain by
+// splits, too, but their executions are ordered by an event (3 us of 56 and more for float64 gradients
+// at O=13, V=81 and larger contractions): a program may run them on several streams, with out bound to
+// other storage in between, and need not know of the partial sums.
+static bool starved(const tamm_plan* p) {
+  int64_t tiles = 0;
+  double max_kext = 0;
+  for (const BlockShape& b : p->shapes) {
+    tiles += ((b.mext + 127) / 128) * ((b.next + 127) / 128) * b.count;
+    max_kext = std::max(max_kext, b.kext);
+  }
+  return tiles < 2 * kComputeUnits && max_kext >= 8 * (p->prec <= TAMM_PREC_F32 ? 16 : 32);
+}
+
 // Work decomposition for one kernel configuration: macro-tiles of every stored output block,
 // heaviest first (longest-processing-time order), with the K splits of a tile adjacent, then laid
 // out for the dies (xcd_order).
@@ -1001,6 +1021,7 @@ static int configure_work(tamm_plan* p, int config, int k_splits) {
   p->queued = p->prec == TAMM_PREC_F64 && !p->no_queue && queue_pays(p->stats.useful_flops, p->work.size(), f);
   if (p->queued) queue_order(p->work, 0, chunk, p->queue_begin);
   else xcd_order(p->work, chunk);
+  p->serial = k_splits > 1 && !starved(p);
   p->config = config;
   p->k_splits = k_splits;
   p->stats.work_items = (int64_t)p->work.size();
@@ -1144,22 +1165,7 @@ extern "C" int tamm_plan_screen(tamm_plan* p, void* stream) {
   return rc == TAMM_OK ? ok() : rc;
 }
 
-// The persistent launch of long items, after the screening if `screen` (which then clears its counters).
-static int queue_launch(tamm_plan* p, ContractParams& cp, int layout, bool screen, hipStream_t s) {
-  std::lock_guard<std::mutex> lock(p->sets.mu);
-  int set = -1;
-  int rc = p->sets.take(s, &set);
-  if (rc != TAMM_OK) return rc;
-  if (set >= 0) {
-    cp.queue_next = (int32_t*)(p->ws + p->off_queue) + set * kQueues;
-    std::copy(p->queue_begin, p->queue_begin + kQueues + 1, cp.queue_begin);
-    if (!screen) HIP_TRY(launch_clear_queues(cp.queue_next, s));
-  }
-  if (screen && (rc = screen_launch(p, cp.queue_next, s)) != TAMM_OK) return rc;
-  HIP_TRY(launch_contract_f64(p->config, layout, cp, set >= 0 ? p->queue_grid : 0, s));
-  return p->sets.launched(set, s);
-}
-
+// The contraction, after the screening if `screen` (which then clears the queue counters).
 static int contract_launch(tamm_plan* p, double alpha, double beta, bool screen, hipStream_t s) {
   ContractParams cp{};
   cp.single = problem_desc(p, p->ws, p->lay, p->k_splits > 1 ? (double*)(p->ws + p->off_partial) : nullptr, p->k_splits,
@@ -1168,17 +1174,21 @@ static int contract_launch(tamm_plan* p, double alpha, double beta, bool screen,
   cp.work = (const WorkItem*)(p->ws + p->off_work);
   cp.n_work = (int32_t)p->work.size();
   const int layout = gather_layout(p);
-  if (screen && !p->queued) {
-    const int rc = screen_launch(p, nullptr, s);
-    if (rc != TAMM_OK) return rc;
+  std::unique_lock<std::mutex> lock(p->sets.mu, std::defer_lock);
+  const bool shared = p->queued || p->serial;
+  int set = -1, rc = TAMM_OK;
+  if (shared) {
+    lock.lock();
+    if ((rc = p->sets.take(s, p->queued, p->serial, &set)) != TAMM_OK) return rc;
   }
+  if (p->queued && set >= 0) {
+    cp.queue_next = (int32_t*)(p->ws + p->off_queue) + set * kQueues;
+    std::copy(p->queue_begin, p->queue_begin + kQueues + 1, cp.queue_begin);
+    if (!screen) HIP_TRY(launch_clear_queues(cp.queue_next, s));
+  }
+  if (screen && (rc = screen_launch(p, cp.queue_next, s)) != TAMM_OK) return rc;
   if (p->prec == TAMM_PREC_F64) {
-    if (p->queued) {
-      const int rc = queue_launch(p, cp, layout, screen, s);
-      if (rc != TAMM_OK) return rc;
-    } else {
-      HIP_TRY(launch_contract_f64(p->config, layout, cp, 0, s));
-    }
+    HIP_TRY(launch_contract_f64(p->config, layout, cp, cp.queue_next ? p->queue_grid : 0, s));
   } else {
     if (p->prec != TAMM_PREC_F32) {
       // operand split into packed bfloat16 slices, then the contraction reads the split copies
@@ -1225,7 +1235,7 @@ static int contract_launch(tamm_plan* p, double alpha, double beta, bool screen,
     r.tile_n = f.nt;
     HIP_TRY(launch_reduce(r, s));
   }
-  return TAMM_OK;
+  return shared ? p->sets.launched(set, s) : TAMM_OK;
 }
 
 extern "C" int tamm_plan_contract(tamm_plan* p, double alpha, double beta, void* stream) {

@@ -1,6 +1,6 @@
-"""Launches of one plan that overlap: on more streams than the plan has counter sets, and in captured
-graphs (more of them than there are sets for) beside eager launches, each with an output of its own.
-Every output must hold the bits that the plan writes alone."""
+"""Launches of one plan that overlap: on more streams than the plan has counter sets, with partial sums
+of K splits, and in captured graphs (more of them than there are sets for) beside eager launches, each
+with an output of its own.  Every output must hold the bits that the plan writes alone."""
 
 import pytest
 import torch
@@ -10,15 +10,16 @@ from paper_2201_01257_amd import core as tm
 pytestmark = pytest.mark.gpu
 
 
-def queued_plan():
-    # 576 tiles of 128 x 128, about 60 us each: more items than resident workgroups, long enough for the queues
-    m, k = tm.Space.explicit([1500, 1500]), tm.Space.explicit([200, 56])
+def long_plan(k_tiles=(200, 56), k_splits=1):
+    # 576 tiles of 128 x 128: more items than resident workgroups; 256 summed indices and more (about
+    # 60 us) make them long enough for the queues, and so do parts of that length
+    m, k = tm.Space.explicit([1500, 1500]), tm.Space.explicit(list(k_tiles))
     A, B, C = tm.Tensor([m, k]), tm.Tensor([k, m]), tm.Tensor([m, m])
     g = torch.Generator(device="cuda").manual_seed(11)
     for t in (A, B):
         t.data.copy_(torch.randn(t.data.shape, dtype=torch.float64, device="cuda", generator=g))
     plan = tm.Plan(C, "ij", A, "ik", B, "kj")
-    plan.set_config(3, 1)
+    plan.set_config(3, k_splits)
     plan.execute(1.0, 0.0)
     torch.cuda.synchronize()
     want = C.data.clone()
@@ -27,8 +28,10 @@ def queued_plan():
     return plan, C, want
 
 
-def test_launches_on_more_streams_than_counter_sets():
-    plan, C, want = queued_plan()
+# one part from the queues; two parts from a plain launch; two parts from the queues
+@pytest.mark.parametrize("k_tiles,k_splits", [((200, 56), 1), ((40, 40), 2), ((256, 256), 2)])
+def test_launches_on_more_streams_than_counter_sets(k_tiles, k_splits):
+    plan, C, want = long_plan(k_tiles, k_splits)
     streams = [torch.cuda.Stream() for _ in range(12)]
     outs = [torch.full_like(want, float("nan")) for _ in range(36)]
     torch.cuda.synchronize()
@@ -41,7 +44,7 @@ def test_launches_on_more_streams_than_counter_sets():
 
 
 def test_captured_launches_beside_eager_ones():
-    plan, C, want = queued_plan()
+    plan, C, want = long_plan()
     outs = [torch.full_like(want, float("nan")) for _ in range(30)]
     graphs = []
     for out in outs[:26]:  # two more than there are sets for captured launches
@@ -67,7 +70,7 @@ def test_captured_launches_beside_eager_ones():
 
 
 def test_contractions_after_one_screening():
-    plan, C, want = queued_plan()
+    plan, C, want = long_plan()
     plan.screen()
     for _ in range(3):  # no screening in between to clear the counters
         C.data.fill_(float("nan"))
