@@ -19,8 +19,12 @@ int ok();
 // Drops the cached one-shot plans that name tensor t (called when t is destroyed).
 void contract_cache_evict(const tamm_tensor* t);
 
+// One-shot contractions in a workspace of `limit` bytes.
 int contract_workspace_within(tamm_tensor* out, const char* out_lbl, const tamm_tensor* lhs, const char* lhs_lbl,
                               const tamm_tensor* rhs, const char* rhs_lbl, int32_t precision, size_t limit, size_t* bytes);
+int contract_within(tamm_tensor* out, const char* out_lbl, const tamm_tensor* lhs, const char* lhs_lbl, const tamm_tensor* rhs,
+                    const char* rhs_lbl, int32_t precision, size_t limit, double alpha, double beta, void* workspace, size_t bytes,
+                    void* stream);
 
 // AddOp enqueue (addop.cpp), shared with the scheduler.
 int add_enqueue(tamm_add* a, double alpha, double beta, hipStream_t s);

@@ -55,5 +55,5 @@ extern "C" int tamm_contract_noalloc(tamm_tensor* out, const char* out_lbl, cons
     }
     ptr = g_scratch_ptr[dev];
   }
-  return tamm_contract(out, out_lbl, lhs, lhs_lbl, rhs, rhs_lbl, precision, alpha, beta, ptr, kScratchBytes, stream);
+  return contract_within(out, out_lbl, lhs, lhs_lbl, rhs, rhs_lbl, precision, kScratchBytes, alpha, beta, ptr, kScratchBytes, stream);
 }

@@ -199,7 +199,7 @@ struct tamm_plan {
   int tile_order = 0;              // 0: tiles of a block row by row; 1: grouped by B column panel
   std::vector<WorkItem> work;
   bool queued = false;             // persistent launch over the dies' queues (float64, more items than resident workgroups)
-  bool no_queue = false;           // never (tamm_contract_noalloc keeps its workspace as small as it was)
+  size_t ws_limit = 0;             // the caller's workspace, when it is fixed (tamm_contract_noalloc); 0: any size
   int32_t queue_begin[kQueues + 1] = {};
   bool serial = false;             // eager launches one after another: they share partial sums
   int queue_grid = 0;              // workgroups of a persistent launch on the device it is bound on
@@ -1018,7 +1018,11 @@ static int configure_work(tamm_plan* p, int config, int k_splits) {
   for (const Part& q : parts) p->work.push_back(q.w);
   if (p->work.size() > (size_t)INT32_MAX / 2) return fail(TAMM_ERR_UNSUPPORTED, "too many work items");
   const int chunk = p->xcd_chunk >= 0 ? p->xcd_chunk : xcd_chunk();
-  p->queued = p->prec == TAMM_PREC_F64 && !p->no_queue && queue_pays(p->stats.useful_flops, p->work.size(), f);
+  p->queued = p->prec == TAMM_PREC_F64 && queue_pays(p->stats.useful_flops, p->work.size(), f);
+  if (p->queued && p->ws_limit > 0) {  // the counters must not be what a fixed workspace lacks room for
+    layout_workspace(p, f, p->work.size(), p->reduce.size(), (size_t)slots, true);
+    p->queued = p->ws_size <= p->ws_limit;
+  }
   if (p->queued) queue_order(p->work, 0, chunk, p->queue_begin);
   else xcd_order(p->work, chunk);
   p->serial = k_splits > 1 && !starved(p);
@@ -1323,8 +1327,9 @@ struct ContractKey {
   const tamm_tensor* rhs;
   std::string labels;  // out, lhs and rhs labels joined by '/'
   int32_t precision;
+  size_t limit;  // of the workspace, 0: none
   bool operator<(const ContractKey& o) const {
-    return std::tie(out, lhs, rhs, labels, precision) < std::tie(o.out, o.lhs, o.rhs, o.labels, o.precision);
+    return std::tie(out, lhs, rhs, labels, precision, limit) < std::tie(o.out, o.lhs, o.rhs, o.labels, o.precision, o.limit);
   }
 };
 
@@ -1344,19 +1349,31 @@ ContractCache& contract_cache() {
   return *c;
 }
 
-// The cached plan for a contraction, created on first use.  The caller holds the cache lock.
+// The cached plan for a contraction, created on first use.  The caller holds the cache lock.  With a
+// limit of the workspace: the plan without one if that fits, else a plan of its own.
 int cached_plan(ContractCache& c, tamm_tensor* out, const char* ol, const tamm_tensor* lhs, const char* ll,
-                const tamm_tensor* rhs, const char* rl, int32_t precision, tamm_plan** plan) {
+                const tamm_tensor* rhs, const char* rl, int32_t precision, size_t limit, tamm_plan** plan) {
+  if (limit > 0) {
+    const int rc = cached_plan(c, out, ol, lhs, ll, rhs, rl, precision, 0, plan);
+    if (rc != TAMM_OK || (*plan)->ws_size <= limit) return rc;
+  }
   if (!out || !lhs || !rhs || !ol || !ll || !rl) return fail(TAMM_ERR_ARG, "null tensor or label string");
-  ContractKey key{out, lhs, rhs, std::string(ol) + "/" + ll + "/" + rl, precision};
+  ContractKey key{out, lhs, rhs, std::string(ol) + "/" + ll + "/" + rl, precision, limit};
   auto it = c.plans.find(key);
   if (it != c.plans.end()) {
     *plan = it->second.get();
     return TAMM_OK;
   }
   tamm_plan* p = nullptr;
-  const int rc = tamm_plan_create(out, ol, lhs, ll, rhs, rl, (tamm_precision)precision, &p);
+  int rc = tamm_plan_create(out, ol, lhs, ll, rhs, rl, (tamm_precision)precision, &p);
   if (rc != TAMM_OK) return rc;
+  if (limit > 0) {
+    p->ws_limit = limit;
+    if ((rc = configure_work(p, -1, 0)) != TAMM_OK) {
+      delete p;
+      return rc;
+    }
+  }
   c.plans.emplace(std::move(key), std::unique_ptr<tamm_plan>(p));
   *plan = p;
   return TAMM_OK;
@@ -1384,37 +1401,44 @@ extern "C" int tamm_contract_workspace_size(tamm_tensor* out, const char* out_lb
   ContractCache& c = contract_cache();
   std::lock_guard<std::mutex> lock(c.mu);
   tamm_plan* p = nullptr;
-  const int rc = cached_plan(c, out, out_lbl, lhs, lhs_lbl, rhs, rhs_lbl, precision, &p);
+  const int rc = cached_plan(c, out, out_lbl, lhs, lhs_lbl, rhs, rhs_lbl, precision, 0, &p);
   if (rc != TAMM_OK) return rc;
   *bytes = p->ws_size;
   return ok();
 }
 
-// Workspace of the cached plan for a caller with `limit` bytes: without the queue counters when
-// they alone would put it past the limit.
+// Workspace that a caller with `limit` bytes needs.
 int tamm::contract_workspace_within(tamm_tensor* out, const char* out_lbl, const tamm_tensor* lhs, const char* lhs_lbl,
                                     const tamm_tensor* rhs, const char* rhs_lbl, int32_t precision, size_t limit, size_t* bytes) {
   ContractCache& c = contract_cache();
   std::lock_guard<std::mutex> lock(c.mu);
   tamm_plan* p = nullptr;
-  int rc = cached_plan(c, out, out_lbl, lhs, lhs_lbl, rhs, rhs_lbl, precision, &p);
+  const int rc = cached_plan(c, out, out_lbl, lhs, lhs_lbl, rhs, rhs_lbl, precision, limit, &p);
   if (rc != TAMM_OK) return rc;
-  if (p->ws_size > limit && p->queued) {
-    p->no_queue = true;
-    rc = configure_work(p, p->config, p->k_splits);
-    if (rc != TAMM_OK) return rc;
-  }
   *bytes = p->ws_size;
+  if (p->ws_size > limit)  // to be refused: the plan made for the limit is of no use
+    for (auto it = c.plans.begin(); it != c.plans.end(); ++it)
+      if (it->second.get() == p) {
+        c.plans.erase(it);
+        break;
+      }
   return TAMM_OK;
 }
 
 extern "C" int tamm_contract(tamm_tensor* out, const char* out_lbl, const tamm_tensor* lhs, const char* lhs_lbl,
                              const tamm_tensor* rhs, const char* rhs_lbl, int32_t precision, double alpha, double beta,
                              void* workspace, size_t bytes, void* stream) {
+  return contract_within(out, out_lbl, lhs, lhs_lbl, rhs, rhs_lbl, precision, 0, alpha, beta, workspace, bytes, stream);
+}
+
+// tamm_contract with the plan for a caller whose workspace is `limit` bytes (0: tamm_contract's own).
+int tamm::contract_within(tamm_tensor* out, const char* out_lbl, const tamm_tensor* lhs, const char* lhs_lbl,
+                          const tamm_tensor* rhs, const char* rhs_lbl, int32_t precision, size_t limit, double alpha, double beta,
+                          void* workspace, size_t bytes, void* stream) {
   ContractCache& c = contract_cache();
   std::lock_guard<std::mutex> lock(c.mu);
   tamm_plan* p = nullptr;
-  int rc = cached_plan(c, out, out_lbl, lhs, lhs_lbl, rhs, rhs_lbl, precision, &p);
+  int rc = cached_plan(c, out, out_lbl, lhs, lhs_lbl, rhs, rhs_lbl, precision, limit, &p);
   if (rc != TAMM_OK) return rc;
   const auto h = c.holder.find(workspace);
   const bool holds = p->ws_bound && p->ws == (char*)workspace && p->ws_bytes == bytes && h != c.holder.end() &&
