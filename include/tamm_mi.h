@@ -325,10 +325,12 @@ int tamm_contract_cache_clear(void);
  * harnesses that forbid hipMalloc): tamm_contract with no workspace argument.  The workspace is a
  * file-scope device array of the library, TAMM_NOALLOC_WORKSPACE_BYTES (64 MiB) on each GPU the
  * library runs on, held until the process ends; the call allocates nothing (no
- * hipMalloc, no library allocation).  Same operation, arguments, plan cache and results as
- * tamm_contract on the current device; the stream must belong to that device.  ERR_WORKSPACE,
- * before anything is enqueued, when the contraction needs more workspace than the array holds
- * (host check, tamm_contract_workspace_size).  All calls on one GPU share its array, which keeps
+ * hipMalloc, no library allocation).  Same operation, arguments and plan cache as tamm_contract on the
+ * current device; the stream must belong to that device.  Where tamm_contract's plan needs more
+ * workspace than the array holds, the configuration and K splits with the least estimated time that
+ * fit it run instead (a plan of its own in the cache; sums in another order than tamm_contract's),
+ * otherwise the same plan with the same results.  ERR_WORKSPACE, before anything is enqueued, when
+ * none fits (host check).  All calls on one GPU share its array, which keeps
  * the last call's contents (nothing in it needs to start zeroed); calls that overlap in time on one
  * GPU race on it and must be serialised by the caller.  Switching the array between contractions
  * re-uploads the plan tables after draining the device, as tamm_contract does. */

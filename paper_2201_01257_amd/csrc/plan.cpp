@@ -752,11 +752,84 @@ static double group_estimate_us(const std::vector<BlockShape>& shapes, const Til
   return std::max(std::max(longest, total / slots + kGroupTail * longest), bytes / (f.resident > 2 ? 4.8e6 : 3.8e6));
 }
 
+// Workspace layout of a plan: static tables and pair lists, work list, reduce list, queue counters,
+// partial tiles, and for the split-bfloat16 precisions the split operands.
+static void layout_workspace(tamm_plan* p, const TileCfg& f, size_t items, size_t reduces, size_t partials, bool queued) {
+  p->lay = make_layout(p, 0);
+  size_t off = p->lay.end;
+  p->off_work = off;
+  off = align256(off + items * sizeof(WorkItem));
+  p->off_reduce = off;
+  off = align256(off + reduces * sizeof(ReduceItem));
+  p->off_queue = off;
+  if (queued) off = align256(off + (kEagerSets + kCapturedSets) * kQueues * sizeof(int32_t));
+  p->off_partial = off;
+  if (partials > 0) off = align256(off + partials * f.mt * f.nt * sizeof(double));
+  if (p->prec == TAMM_PREC_BF16X3 || p->prec == TAMM_PREC_BF16X4_ALIGNED) {
+    p->off_prepA = off;
+    off = align256(off + p->prepA.size() * sizeof(PrepBlock));
+    p->off_prepB = off;
+    off = align256(off + p->prepB.size() * sizeof(PrepBlock));
+    p->off_xA = off;
+    off = align256(off + (size_t)p->A->numel * sizeof(uint64_t));
+    p->off_xB = off;
+    off = align256(off + (size_t)p->B->numel * sizeof(uint64_t));
+  }
+  p->ws_size = std::max<size_t>(off, 256);
+}
+
+// Workspace sizes of a plan's configurations, without building their work lists.
+struct WorkspaceSizes {
+  tamm_plan size_only;
+  const std::vector<BlockShape>& shapes;
+  double max_kext = 0;
+
+  explicit WorkspaceSizes(const tamm_plan* p) : shapes(p->shapes) {
+    size_only.A = p->A;
+    size_only.B = p->B;
+    size_only.prec = p->prec;
+    size_only.pool.resize(p->pool.size());
+    size_only.blocks.resize(p->blocks.size());
+    size_only.n_kt = p->n_kt;
+    size_only.prepA.resize(p->prepA.size());
+    size_only.prepB.resize(p->prepB.size());
+    for (const BlockShape& b : shapes) max_kext = std::max(max_kext, b.kext);
+  }
+  // 0: configure_work refuses it
+  size_t bytes(const TileCfg& f, int k_splits, bool queued) {
+    size_t items = 0, reduces = 0, partials = 0;
+    for (const BlockShape& b : shapes) {
+      const int ns = block_splits(k_splits, b.kext, max_kext);
+      const size_t tiles = (size_t)(((b.mext + f.mt - 1) / f.mt) * ((b.next + f.nt - 1) / f.nt) * b.count);
+      items += tiles * ns;
+      if (ns > 1) reduces += tiles;
+      if (ns > 1) partials += tiles * ns;
+    }
+    if (partials > (size_t)INT32_MAX / 2 || items > (size_t)INT32_MAX / 2) return 0;
+    layout_workspace(&size_only, f, items, reduces, partials, queued);
+    return size_only.ws_size;
+  }
+};
+
+// The largest workspace of any configuration with 1, 2, .. max_splits K splits.
+size_t tamm::plan_candidate_workspace(const tamm_plan* p, int max_splits) {
+  WorkspaceSizes sizes(p);
+  size_t most = 0;
+  for (int c = 0; c < cfg_count(p->prec); ++c) {
+    if (p->prec == TAMM_PREC_F64 && f64_config_canonical(c) != c) continue;
+    const TileCfg f = cfg_get(p->prec, c);
+    for (int ks = 1; ks <= max_splits; ks *= 2) most = std::max(most, sizes.bytes(f, ks, p->prec == TAMM_PREC_F64));
+  }
+  return most;
+}
+
 // Default configuration and K splits of a plan: the least estimate; more splits only where they are
 // estimated to gain 3 %, never of sums shorter than eight chunks in float64 and float32 (what they gain
 // is what ordering overlapping executions costs, see `starved`: ring at O=5, V=45 16 us in four parts,
 // 19 in one, 20 in four with the event; in split bfloat16 at O=9, V=37 35, 43 and 38), and in float64 8 % above a millisecond, where the queues have filled the tail
-// that splits would (ladder and its gradients at O=32, V=160: 3.1 ms in one part, 3.4 in four).  The partial tiles take at most an eighth of the tensors' bytes or 64 MiB.
+// that splits would (ladder and its gradients at O=32, V=160: 3.1 ms in one part, 3.4 in four).  The partial
+// tiles take at most an eighth of the tensors' bytes or 64 MiB, and the whole workspace no more than the
+// plan's limit.
 static std::pair<int, int> default_work(const tamm_plan* p, int config, int k_splits) {
   const bool f64 = p->prec == TAMM_PREC_F64, split_bf16 = !f64 && p->prec != TAMM_PREC_F32;
   const double bytes = p->stats.algorithmic_bytes, budget = std::max(bytes / 8, (double)(64 << 20));
@@ -764,6 +837,9 @@ static std::pair<int, int> default_work(const tamm_plan* p, int config, int k_sp
   std::pair<int, int> pick(std::max(config, 0), std::max(k_splits, 1));
   for (const BlockShape& b : p->shapes) max_kext = std::max(max_kext, b.kext);
   const bool short_sums = !split_bf16 && max_kext < 8 * 16;
+  std::unique_ptr<WorkspaceSizes> sizes;
+  if (p->ws_limit > 0) sizes = std::make_unique<WorkspaceSizes>(p);
+  size_t smallest = SIZE_MAX;
   for (int ks : {1, 2, 4, 8, 16}) {
     if (ks > 1 && (k_splits > 0 || short_sums)) break;
     const int splits = k_splits > 0 ? k_splits : ks;
@@ -778,6 +854,16 @@ static std::pair<int, int> default_work(const tamm_plan* p, int config, int k_sp
         if (ns > 1) need += 8.0 * f.mt * f.nt * ns * (double)(((b.mext + f.mt - 1) / f.mt) * ((b.next + f.nt - 1) / f.nt) * b.count);
       }
       if (k_splits <= 0 && need > budget) continue;
+      if (sizes) {  // a fixed workspace: what fits, or the smallest (the caller refuses it)
+        const size_t n = sizes->bytes(f, splits, false);
+        if (n == 0 || n > p->ws_limit) {
+          if (n > 0 && best == 1e300 && n < smallest) {
+            smallest = n;
+            pick = std::make_pair(c, splits);
+          }
+          continue;
+        }
+      }
       const double t = estimate_us(p->shapes, f, splits, bytes, split_bf16 ? kTailSplit : kTail);
       if (t < least) {
         least = t;
@@ -868,67 +954,6 @@ static int xcd_chunk() {
     return e ? std::max(0, atoi(e)) : 32;
   }();
   return v;
-}
-
-// Workspace layout of a plan: static tables and pair lists, work list, reduce list, queue counters,
-// partial tiles, and for the split-bfloat16 precisions the split operands.
-static void layout_workspace(tamm_plan* p, const TileCfg& f, size_t items, size_t reduces, size_t partials, bool queued) {
-  p->lay = make_layout(p, 0);
-  size_t off = p->lay.end;
-  p->off_work = off;
-  off = align256(off + items * sizeof(WorkItem));
-  p->off_reduce = off;
-  off = align256(off + reduces * sizeof(ReduceItem));
-  p->off_queue = off;
-  if (queued) off = align256(off + (kEagerSets + kCapturedSets) * kQueues * sizeof(int32_t));
-  p->off_partial = off;
-  if (partials > 0) off = align256(off + partials * f.mt * f.nt * sizeof(double));
-  if (p->prec == TAMM_PREC_BF16X3 || p->prec == TAMM_PREC_BF16X4_ALIGNED) {
-    p->off_prepA = off;
-    off = align256(off + p->prepA.size() * sizeof(PrepBlock));
-    p->off_prepB = off;
-    off = align256(off + p->prepB.size() * sizeof(PrepBlock));
-    p->off_xA = off;
-    off = align256(off + (size_t)p->A->numel * sizeof(uint64_t));
-    p->off_xB = off;
-    off = align256(off + (size_t)p->B->numel * sizeof(uint64_t));
-  }
-  p->ws_size = std::max<size_t>(off, 256);
-}
-
-// The largest workspace of any configuration with 1, 2, .. max_splits K splits, without building
-// their work lists.
-size_t tamm::plan_candidate_workspace(const tamm_plan* p, int max_splits) {
-  tamm_plan size_only;
-  size_only.A = p->A;
-  size_only.B = p->B;
-  size_only.prec = p->prec;
-  size_only.pool.resize(p->pool.size());
-  size_only.blocks.resize(p->blocks.size());
-  size_only.n_kt = p->n_kt;
-  size_only.prepA.resize(p->prepA.size());
-  size_only.prepB.resize(p->prepB.size());
-  double max_kext = 0;
-  for (const BlockShape& b : p->shapes) max_kext = std::max(max_kext, b.kext);
-  size_t most = 0;
-  for (int c = 0; c < cfg_count(p->prec); ++c) {
-    if (p->prec == TAMM_PREC_F64 && f64_config_canonical(c) != c) continue;
-    const TileCfg f = cfg_get(p->prec, c);
-    for (int ks = 1; ks <= max_splits; ks *= 2) {
-      size_t items = 0, reduces = 0, partials = 0;
-      for (const BlockShape& b : p->shapes) {
-        const int ns = block_splits(ks, b.kext, max_kext);
-        const size_t tiles = (size_t)(((b.mext + f.mt - 1) / f.mt) * ((b.next + f.nt - 1) / f.nt) * b.count);
-        items += tiles * ns;
-        if (ns > 1) reduces += tiles;
-        if (ns > 1) partials += tiles * ns;
-      }
-      if (partials > (size_t)INT32_MAX / 2 || items > (size_t)INT32_MAX / 2) continue;  // configure_work refuses it
-      layout_workspace(&size_only, f, items, reduces, partials, p->prec == TAMM_PREC_F64);
-      most = std::max(most, size_only.ws_size);
-    }
-  }
-  return most;
 }
 
 // An output of fewer than two 128 x 128 tiles per compute unit, and sums of eight chunks and more: only

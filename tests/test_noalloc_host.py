@@ -53,3 +53,16 @@ def test_a_refused_call_leaves_no_plan_behind():
     plans = tm.contract_cache_count()
     assert noalloc_status(args, "f64") == "TAMM_ERR_WORKSPACE"
     assert tm.contract_cache_count() == plans
+
+
+# Unsplit, each of these fits the scratch array; the K splits that tamm_contract's plan takes do not, in
+# float32 for the first eight and in float64 for the first six.
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("shape", [(22, 119, 13, 41), (22, 125, 12, 36), (30, 150, 30, 30), (25, 173, 24, 38), (32, 160, 32, 32),
+                                   (32, 160, 16, 40), (20, 160, 20, 64), (8, 200, 8, 50), (40, 200, 40, 40), (12, 40, 3, 3)])
+def test_noalloc_runs_what_fits_without_splits(shape, precision):
+    args = statement("ladder", *shape)
+    plan = tm.Plan(*args, precision=precision, bind=False)
+    plan.set_config(3, 1)
+    assert plan.workspace_size() <= _lib.NOALLOC_WORKSPACE_BYTES
+    assert noalloc_status(args, precision) != "TAMM_ERR_WORKSPACE"
