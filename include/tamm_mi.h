@@ -373,7 +373,10 @@ int tamm_group_set_config(tamm_group* g, int32_t config, int32_t grid);
 int tamm_group_execute(tamm_group* g, const double* alpha, const double* beta, void* stream);
 /* Capture the group's launches (screening, which clears the queue counters, and contractions; no memset or
  * copy nodes) into a hipGraph on an internal stream, with alpha/beta fixed at these values;
- * later tamm_group_execute calls with the same values replay it on their stream. */
+ * later tamm_group_execute calls with the same values replay it on their stream.  A group of several
+ * classes must have been launched outside a capture before (tamm_group_execute, or an autotuner that
+ * measured), else ERR_UNSUPPORTED: several such groups captured first of all and replayed in turn have
+ * ended in a fault on the host.  The same holds for tamm_sched_capture and for the caller's own captures. */
 int tamm_group_capture(tamm_group* g, const double* alpha, const double* beta, void* stream);
 /* Autotuner for groups: for every class separately, every kernel configuration with persistent
  * grids of 1, 2 and 4 workgroups per compute unit and the occupancy-sized grid, the class's launch

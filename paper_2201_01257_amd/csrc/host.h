@@ -44,6 +44,7 @@ int group_create_nodes(const std::vector<std::vector<tamm_plan*>>& nodes, tamm_g
 int group_enqueue(tamm_group* g, hipStream_t s);
 int group_update_desc(tamm_group* g, const double* alpha, const double* beta, hipStream_t s, bool* changed);
 int group_check_bound(tamm_group* g);
+int group_check_capture(const tamm_group* g);
 int group_autotune(tamm_group* g, hipStream_t s, const char* cache_path, int32_t reps);
 size_t group_workspace_size(const tamm_group* g);
 size_t group_autotune_workspace_size(tamm_group* g);

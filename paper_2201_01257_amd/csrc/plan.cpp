@@ -1725,6 +1725,7 @@ struct tamm_group {
   hipStream_t side[kLayouts] = {};
   hipEvent_t ev_fork = nullptr;
   hipEvent_t ev_join[kLayouts] = {};
+  bool ran = false;  // launched outside a capture
 };
 
 static void group_drop_graph(tamm_group* g) {
@@ -2096,9 +2097,35 @@ static int group_enqueue_class(tamm_group* g, int c, bool cleared, hipStream_t s
 
 namespace tamm {
 
+// TAMM_GROUP_SERIAL: the layout classes' launches one after another.
+static bool group_serial() {
+  static const bool v = [] {
+    const char* e = getenv("TAMM_GROUP_SERIAL");
+    return e && atoi(e) != 0;
+  }();
+  return v;
+}
+
+// Whether the group may be captured.  Several groups of several layout classes, captured before their
+// first launch outside a capture, alive together and replayed in turn, have ended in a segmentation
+// fault on the host whose cause is not known; that order is refused.
+int group_check_capture(const tamm_group* g) {
+  int present = 0;
+  for (int c = 0; c < kLayouts; ++c) present += g->cls_begin[c + 1] > g->cls_begin[c] ? 1 : 0;
+  if (present > 1 && !g->ran && !group_serial())
+    return fail(TAMM_ERR_UNSUPPORTED, "a group of several gather layouts must be executed once before it is captured");
+  return TAMM_OK;
+}
+
 // Enqueue the group's kernels (screening, which clears the queue counters, then each class's
 // contraction), consuming the descriptors in the workspace.
 int group_enqueue(tamm_group* g, hipStream_t s) {
+  if (!g->ran) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(s, &status));
+    if (status == hipStreamCaptureStatusNone) g->ran = true;
+    else if (const int rc = group_check_capture(g)) return rc;
+  }
   ScreenParams sp{};
   sp.probs = (const ScreenDesc*)(g->ws + g->off_sdesc);
   sp.item_prob = (const int32_t*)(g->ws + g->off_sitems);
@@ -2116,11 +2143,7 @@ int group_enqueue(tamm_group* g, hipStream_t s) {
   int present[kLayouts], np = 0;
   for (int c = 0; c < kLayouts; ++c)
     if (g->cls_begin[c + 1] > g->cls_begin[c]) present[np++] = c;
-  static const bool serial = [] {
-    const char* e = getenv("TAMM_GROUP_SERIAL");
-    return e && atoi(e) != 0;
-  }();
-  if (np <= 1 || serial) {
+  if (np <= 1 || group_serial()) {
     for (int i = 0; i < np; ++i) {
       const int rc = group_enqueue_class(g, present[i], true, s);
       if (rc != TAMM_OK) return rc;
@@ -2226,6 +2249,7 @@ extern "C" int tamm_group_execute(tamm_group* g, const double* alpha, const doub
 extern "C" int tamm_group_capture(tamm_group* g, const double* alpha, const double* beta, void* stream) {
   if (!g || !alpha || !beta) return fail(TAMM_ERR_ARG, "null argument");
   int rc = group_check(g);
+  if (rc == TAMM_OK) rc = group_check_capture(g);
   if (rc != TAMM_OK) return rc;
   hipStream_t s = (hipStream_t)stream;
   bool changed = false;

@@ -425,6 +425,8 @@ extern "C" int tamm_sched_capture(tamm_sched* s, void* stream) {
   if (!s) return fail(TAMM_ERR_ARG, "null schedule");
   int rc = sched_check(s);
   if (rc != TAMM_OK) return rc;
+  for (const Level& L : s->levels)
+    if (L.group && (rc = group_check_capture(L.group)) != TAMM_OK) return rc;
   rc = sched_update(s, (hipStream_t)stream);
   if (rc != TAMM_OK) return rc;
   HIP_TRY(hipStreamSynchronize((hipStream_t)stream));

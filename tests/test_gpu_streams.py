@@ -1,6 +1,7 @@
 """Launches of one plan that overlap: on more streams than the plan has counter sets, with partial sums
 of K splits, and in captured graphs (more of them than there are sets for) beside eager launches, each
-with an output of its own.  Every output must hold the bits that the plan writes alone."""
+with an output of its own.  Every output must hold the bits that the plan writes alone.  And the order
+of capture and first execution of a group."""
 
 import pytest
 import torch
@@ -77,3 +78,33 @@ def test_contractions_after_one_screening():
         plan.contract(1.0, 0.0)
         torch.cuda.synchronize()
         assert torch.equal(C.data, want)
+
+
+def test_group_of_several_layouts_is_executed_before_it_is_captured():
+    m, k = tm.Space.explicit([30, 34]), tm.Space.explicit([20, 24])
+    plans = []
+    for (sa, la), (sb, lb) in ((([m, k], "ik"), ([k, m], "kj")), (([k, m], "ki"), ([m, k], "jk"))):
+        A, B, C = tm.Tensor(sa), tm.Tensor(sb), tm.Tensor([m, m])
+        for t in (A, B):
+            t.data.normal_()
+        plans.append(tm.Plan(C, "ij", A, la, B, lb, bind=False))
+    group = tm.Group(plans)
+    with pytest.raises(tm.TammError) as e:
+        group.capture([1.0, 1.0], [0.0, 0.0])
+    assert e.value.status == "TAMM_ERR_UNSUPPORTED"
+    group.execute([1.0, 1.0], [0.0, 0.0])
+    torch.cuda.synchronize()
+    want = [p.out.data.clone() for p in plans]
+    group.capture([1.0, 1.0], [0.0, 0.0])
+    for _ in range(2):
+        for p in plans:
+            p.out.data.fill_(float("nan"))
+        group.execute([1.0, 1.0], [0.0, 0.0])
+        torch.cuda.synchronize()
+        for p, w in zip(plans, want):
+            assert torch.equal(p.out.data, w)
+    group = tm.Group(plans[:1])  # of one layout: captured at once
+    group.capture([1.0], [0.0])
+    group.execute([1.0], [0.0])
+    torch.cuda.synchronize()
+    assert torch.equal(plans[0].out.data, want[0])
