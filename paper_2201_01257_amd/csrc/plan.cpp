@@ -2122,8 +2122,8 @@ int group_check_capture(const tamm_group* g) {
 int group_enqueue(tamm_group* g, hipStream_t s) {
   if (!g->ran) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    HIP_TRY(hipStreamIsCapturing(s, &status));
-    if (status == hipStreamCaptureStatusNone) g->ran = true;
+    if (hipStreamIsCapturing(s, &status) != hipSuccess) (void)hipGetLastError();  // the launches will say it
+    else if (status == hipStreamCaptureStatusNone) g->ran = true;
     else if (const int rc = group_check_capture(g)) return rc;
   }
   ScreenParams sp{};
