@@ -900,9 +900,9 @@ static void cut_extent(int32_t ext, int32_t tile, int32_t unit, std::vector<int3
 // and tiles that read the same rows of A or columns of B run together behind one L2.  Slots left
 // empty by dies with fewer items are squeezed out, which only moves a few tail items to another
 // die.  A chunk of 0 or 1 keeps the list as it is.
-static void xcd_order(std::vector<WorkItem>& work, int chunk) {
+static void xcd_order(std::vector<WorkItem>& work, size_t first, int chunk) {  // items from `first` on
   constexpr int kDies = 8;
-  const size_t n = work.size();
+  const size_t n = work.size() - first;
   if (chunk <= 1 || n <= (size_t)kDies) return;
   const size_t nchunks = (n + chunk - 1) / chunk;
   std::vector<size_t> len(kDies, 0);
@@ -917,8 +917,8 @@ static void xcd_order(std::vector<WorkItem>& work, int chunk) {
   std::vector<WorkItem> out;
   out.reserve(n);
   for (int64_t l : slot)
-    if (l >= 0) out.push_back(work[(size_t)l]);
-  work.swap(out);
+    if (l >= 0) out.push_back(work[first + (size_t)l]);
+  std::copy(out.begin(), out.end(), work.begin() + first);
 }
 
 // The same chunks as the queues of a persistent launch: chunk c of the longest-first list goes to
@@ -1049,7 +1049,7 @@ static int configure_work(tamm_plan* p, int config, int k_splits) {
     p->queued = p->ws_size <= p->ws_limit;
   }
   if (p->queued) queue_order(p->work, 0, chunk, p->queue_begin);
-  else xcd_order(p->work, chunk);
+  else xcd_order(p->work, 0, chunk);
   p->serial = k_splits > 1 && !starved(p);
   p->config = config;
   p->k_splits = k_splits;
@@ -1690,7 +1690,7 @@ extern "C" int tamm_plan_autotune(tamm_plan* p, void* workspace, size_t bytes, v
 // the same output tiles (a fused node, built by the scheduler): their pair lists are screened
 // into one list per output block and one output tile's K loop runs over all of them.
 // ---------------------------------------------------------------------------------------------
-constexpr int kGroupChunk = 8;  // items per die chunk of a group's queues
+constexpr int kGroupChunk = 8;  // items per die chunk of a group's queues, or of its plain launches
 struct tamm_group {
   std::vector<std::vector<tamm_plan*>> nodes;  // member plans of each node
   std::vector<tamm_plan*> plans;               // every member plan, node by node
@@ -1799,12 +1799,13 @@ static int group_default_config(const tamm_group* g, int layout) {
 
 // Work lists of every layout class with the class's configuration cfgs[c] (< 0: the class's
 // default), each heaviest first, and the workspace layout.
-static int group_configure_classes(tamm_group* g, const int* cfgs) {
+static int group_configure_classes(tamm_group* g, const int* cfgs, const int* grids) {
   for (int c = 0; c < kLayouts; ++c) {
     const int k = cfgs[c] < 0 ? group_default_config(g, c) : cfgs[c];
     if (k >= f64_config_count()) return fail(TAMM_ERR_ARG, "configuration %d does not exist", k);
     g->cfg[c] = k;
   }
+  std::copy(grids, grids + kLayouts, g->grid);
   struct Tile {
     double cost;
     WorkItem w;
@@ -1843,7 +1844,8 @@ static int group_configure_classes(tamm_group* g, const int* cfgs) {
     double flops = 0;
     for (const Tile& t : tiles) flops += 2.0 * t.cost;
     g->queued[c] = queue_pays(flops, tiles.size(), cfg_get(TAMM_PREC_F64, g->cfg[c]));
-    queue_order(g->work, g->cls_begin[c], kGroupChunk, g->queue_begin[c]);
+    if (g->grid[c] > 0 || g->queued[c]) queue_order(g->work, g->cls_begin[c], kGroupChunk, g->queue_begin[c]);
+    else xcd_order(g->work, g->cls_begin[c], kGroupChunk);
   }
   g->cls_begin[kLayouts] = (int32_t)g->work.size();
   size_t off = 0;
@@ -1885,11 +1887,12 @@ static int group_configure_classes(tamm_group* g, const int* cfgs) {
   return TAMM_OK;
 }
 
-// One configuration for every class (< 0: each class's default).
-static int group_configure(tamm_group* g, int config) {
-  int cfgs[kLayouts];
-  for (int c = 0; c < kLayouts; ++c) cfgs[c] = config;
-  return group_configure_classes(g, cfgs);
+// One configuration (< 0: each class's default) and persistent grid (0: automatic) for every class.
+static int group_configure(tamm_group* g, int config, int grid) {
+  int cfgs[kLayouts], grids[kLayouts];
+  std::fill(cfgs, cfgs + kLayouts, config);
+  std::fill(grids, grids + kLayouts, grid);
+  return group_configure_classes(g, cfgs, grids);
 }
 
 // Plans that can share output tiles: float64, the same output tensor, the same flattening of the
@@ -1961,7 +1964,7 @@ int group_create_nodes(const std::vector<std::vector<tamm_plan*>>& nodes, tamm_g
     }
     g->work_capacity += most;
   }
-  const int rc = group_configure(g.get(), -1);
+  const int rc = group_configure(g.get(), -1, 0);
   if (rc != TAMM_OK) return rc;
   *out = g.release();
   return TAMM_OK;
@@ -2068,10 +2071,8 @@ extern "C" int tamm_group_bind_workspace(tamm_group* g, void* dev_ptr, size_t by
 extern "C" int tamm_group_set_config(tamm_group* g, int32_t config, int32_t grid) {
   if (!g) return fail(TAMM_ERR_ARG, "null group");
   if (grid < 0) return fail(TAMM_ERR_ARG, "grid must be >= 0");
-  const int rc = group_configure(g, config);
-  if (rc != TAMM_OK) return rc;
-  for (int c = 0; c < kLayouts; ++c) g->grid[c] = grid;
-  return ok();
+  const int rc = group_configure(g, config, grid);
+  return rc == TAMM_OK ? ok() : rc;
 }
 
 // The contraction launch of one layout class, persistent on the tuned grid or, for long items, on every
@@ -2315,9 +2316,8 @@ int group_autotune(tamm_group* g, hipStream_t s, const char* cache_path, int32_t
       if (f64_config_canonical(k) != k) continue;  // another id of a kernel already timed
       for (int mult : {0, 1, 2, 4}) {  // 0: every resident slot (occupancy-sized grid)
         if (rc != TAMM_OK) break;  // a failed launch ends the search with its error
-        if ((rc = group_configure(g, k)) != TAMM_OK) break;
+        if ((rc = group_configure(g, k, mult * cus)) != TAMM_OK) break;
         if (g->ws_size > bytes) continue;
-        for (int c = 0; c < kLayouts; ++c) g->grid[c] = mult * cus;
         if ((rc = group_bind(g, ws, bytes)) != TAMM_OK) break;
         // screening and a warm-up; alpha = 0, beta = 1 leaves every output unchanged (finite
         // operands), and the classes' launches below reuse that screening
@@ -2343,11 +2343,13 @@ int group_autotune(tamm_group* g, hipStream_t s, const char* cache_path, int32_t
         return fail(TAMM_ERR_WORKSPACE, "no configuration fits the bound workspace");
     for (int c = 0; c < kLayouts; ++c) cache_store(cache_path, g->signature, tag[c], best[c]);
   }
-  int cfgs[kLayouts];
-  for (int c = 0; c < kLayouts; ++c) cfgs[c] = best[c].config;  // < 0 (empty class): default
-  rc = group_configure_classes(g, cfgs);
+  int cfgs[kLayouts], grids[kLayouts];
+  for (int c = 0; c < kLayouts; ++c) {
+    cfgs[c] = best[c].config;  // < 0 (empty class): default
+    grids[c] = best[c].config >= 0 ? best[c].grid : 0;
+  }
+  rc = group_configure_classes(g, cfgs, grids);
   if (rc != TAMM_OK) return rc;
-  for (int c = 0; c < kLayouts; ++c) g->grid[c] = best[c].config >= 0 ? best[c].grid : 0;
   if (g->ws_size > bytes) return fail(TAMM_ERR_WORKSPACE, "cached configuration needs %zu bytes", g->ws_size);
   return group_bind(g, ws, bytes);
 }
