@@ -6,9 +6,11 @@
 #include <cstdlib>
 #include <cstring>
 #include <fstream>
+#include <functional>
 #include <map>
 #include <memory>
 #include <mutex>
+#include <queue>
 #include <sstream>
 #include <string>
 #include <tuple>
@@ -668,7 +670,7 @@ static int block_splits(int k_splits, double kext, double max_kext) {
 // estimate costs 2-3 %, the rule before it 15 % in float32 and 20-40 % in split bfloat16, which it ran
 // on four-wave tiles.
 constexpr double kRoundTrip16 = 0.60, kRoundTrip32 = 0.70, kRoundTripWave = 0.78;  // a chunk of 16, of 32, of a one-wave workgroup
-constexpr double kPair = 0.137, kItem = 3.84, kPer1024 = 0.63, kTail = 0.42, kTailSplit = 0.7, kGroupTail = 0.3;
+constexpr double kPair = 0.137, kItem = 3.84, kPer1024 = 0.63, kTail = 0.42, kTailSplit = 0.7;
 constexpr double kReduce = 5.6, kReduceBytes = 5.0e6;  // launch, bytes per microsecond
 
 static double item_us(const BlockShape& b, const TileCfg& f, double area, double parts) {
@@ -678,7 +680,7 @@ static double item_us(const BlockShape& b, const TileCfg& f, double area, double
   return (chunks * std::max(2.0 * area * f.kt / rate, lat) + (double)b.pairs * kPair) / parts + kItem + kPer1024 * area / 1024.0;
 }
 
-// Tiles of at most tm x tn of the blocks of one shape: fn(area of a tile, how many).
+// Tiles of at most tm x tn of the blocks of one shape: fn(rows, columns, how many).
 template <typename F>
 static void for_tiles(const BlockShape& b, const TileCfg& f, int64_t tm, int64_t tn, F&& fn) {
   const int64_t nm = (b.mext + tm - 1) / tm, um = (b.mext + f.um - 1) / f.um;  // tiles and units of the rows
@@ -686,7 +688,7 @@ static void for_tiles(const BlockShape& b, const TileCfg& f, int64_t tm, int64_t
   for (int hm = 0; hm < 2; ++hm)  // tiles of um / nm units, and the um % nm tiles of one more
     for (int hn = 0; hn < 2; ++hn) {
       const double n = (double)((hm ? um % nm : nm - um % nm) * (hn ? un % nn : nn - un % nn) * b.count);
-      if (n > 0) fn((double)((um / nm + hm) * f.um) * (double)((un / nn + hn) * f.un), n);
+      if (n > 0) fn((double)((um / nm + hm) * f.um), (double)((un / nn + hn) * f.un), n);
     }
 }
 
@@ -697,8 +699,8 @@ static double estimate_us(const std::vector<BlockShape>& shapes, const TileCfg& 
   for (const BlockShape& b : shapes) {
     const int ns = block_splits(k_splits, b.kext, max_kext);
     const double parts = (double)std::min<int64_t>(ns, std::max<int64_t>(1, b.pairs));  // a pair is never cut
-    for_tiles(b, f, f.mt, f.nt, [&](double area, double n) {
-      const double t = item_us(b, f, area, parts);
+    for_tiles(b, f, f.mt, f.nt, [&](double rows, double cols, double n) {
+      const double t = item_us(b, f, rows * cols, parts);
       total += t * n * parts;
       items += n * parts;
       longest = std::max(longest, t);
@@ -728,28 +730,78 @@ static std::pair<int32_t, int32_t> group_tile(const BlockShape& b, const TileCfg
 }
 
 // The limit of group_tile for the members of one launch: the launch's time if evenly spread.  (Of
-// 0.4, 0.7 and 1 times that, 1 gave the best mean over 17 schedules and groups, and no cut tiles at
-// all left the hole-hole intermediate's launch 1.4 times as long at O=26, V=102.)
+// 0.4, 0.7 and 1 times that, 1 gave the best mean over 17 schedules and groups.  Whole tiles leave the
+// hole-hole intermediate's launch 1.4 times as long at O=26, V=102, and make the ladder's at O=29,
+// V=135 in tiles of 19 and 37 5 % shorter: group_default_config estimates both.)
 static double group_limit_us(const std::vector<BlockShape>& shapes, const TileCfg& f) {
   double total = 0;
   for (const BlockShape& b : shapes)
-    for_tiles(b, f, f.mt, f.nt, [&](double area, double n) { total += item_us(b, f, area, 1.0) * n; });
+    for_tiles(b, f, f.mt, f.nt, [&](double rows, double cols, double n) { total += item_us(b, f, rows * cols, 1.0) * n; });
   return total / ((double)f.resident * kComputeUnits);
 }
 
-// Estimated time of a group's launch over blocks of these shapes (estimate_us with cut tiles).
-static double group_estimate_us(const std::vector<BlockShape>& shapes, const TileCfg& f, double bytes) {
-  const double slots = (double)f.resident * kComputeUnits, limit = group_limit_us(shapes, f);
-  double total = 0, longest = 0;
+// End of a launch whose slots take the items, longest first, one after another.  Items and slots are
+// counted by classes of equal time.
+struct ItemClass {
+  double us, n;
+};
+static double longest_first_us(std::vector<ItemClass>& items, double slots) {
+  std::sort(items.begin(), items.end(), [](const ItemClass& x, const ItemClass& y) { return x.us > y.us; });
+  using Slots = std::pair<double, double>;  // when they are free, how many
+  std::priority_queue<Slots, std::vector<Slots>, std::greater<Slots>> free;
+  free.push(Slots(0.0, slots));
+  double end = 0;
+  for (const ItemClass& c : items)
+    for (double left = c.n; left > 0;) {
+      const Slots s = free.top();
+      const double n = std::min(left, s.second);
+      free.pop();
+      if (s.second > n) free.push(Slots(s.first, s.second - n));
+      free.push(Slots(s.first + c.us, n));
+      end = std::max(end, s.first + c.us);
+      left -= n;
+    }
+  return end;
+}
+
+// Estimated time of a group's launch over blocks of these shapes, whole tiles or cut ones.  A launch
+// without K splits has few rounds of items, and cut tiles are slower than their area says, which the
+// plans' estimate (sum over the slots plus part of an item) does not see: with it one contraction in a
+// group lost 10 % to the best configuration and cut (78 contractions, 16 choices each), up to 72 %, and 20 of
+// 48 were slower than with the rule of least padding before it (ladder at O=31, V=126 in tiles of 16 and 42
+// 1.55 -> 2.29 ms).  Here the products' rate falls with a tile's perimeter over its area, the items are
+// dealt out longest first, and slots that fall idle leave their share of the compute unit to the others
+// (kGroupShare of the idle time): 3.5 % lost, up to 40 %.  Constants fitted to the same measurements.
+constexpr double kGroupArea = 0.0124, kGroupPerimeter = 0.240;  // us per MFLOP of the chip, times 1 and perimeter / 2 / area
+constexpr double kGroupTrip16 = 0.54, kGroupTrip32 = 0.60, kGroupTripWave = 0.92;
+constexpr double kGroupPair = 0.151, kGroupItem = 2.09, kGroupPer1024 = 0.735, kGroupShare = 0.58;
+static double group_estimate_us(const std::vector<BlockShape>& shapes, const TileCfg& f, double bytes, bool cut) {
+  const double slots = (double)f.resident * kComputeUnits, limit = cut ? group_limit_us(shapes, f) : 1e300;
+  const double trip = f.threads == 64 ? kGroupTripWave : (f.kt == 32 ? kGroupTrip32 : kGroupTrip16);
+  double total = 0, n_items = 0, alone = 0, longest = 0;  // alone: the longest item with a compute unit to itself
+  std::vector<ItemClass> items;
   for (const BlockShape& b : shapes) {
     const auto tile = group_tile(b, f, limit);
-    for_tiles(b, f, tile.first, tile.second, [&](double area, double n) {
-      const double t = item_us(b, f, area, 1.0);
+    const double chunks = (double)(f.kt == 32 ? b.chunks32 : b.chunks16);
+    for_tiles(b, f, tile.first, tile.second, [&](double rows, double cols, double n) {
+      const double area = rows * cols;
+      const double unit = 2.0 * area * f.kt * (kGroupArea + kGroupPerimeter * (rows + cols) / area) * 1e-6 * kComputeUnits;
+      const double rest = (double)b.pairs * kGroupPair + kGroupItem + kGroupPer1024 * area / 1024.0;
+      const double t = chunks * std::max(unit * f.resident, trip) + rest;
+      items.push_back(ItemClass{t, n});
       total += t * n;
+      n_items += n;
       longest = std::max(longest, t);
+      alone = std::max(alone, chunks * std::max(unit, trip) + rest);
     });
   }
-  return std::max(std::max(longest, total / slots + kGroupTail * longest), bytes / (f.resident > 2 ? 4.8e6 : 3.8e6));
+  double t = alone;
+  if (n_items > kComputeUnits) {
+    // of many rounds the last leaves half an item's time on average
+    const double even = total / slots, end = n_items > 16 * slots ? even + 0.5 * longest : longest_first_us(items, slots);
+    t = std::max(alone, end - kGroupShare * (end - even));
+  }
+  return std::max(t, bytes / (f.resident > 2 ? 4.8e6 : 3.8e6));
 }
 
 // Workspace layout of a plan: static tables and pair lists, work list, reduce list, queue counters,
@@ -1780,28 +1832,34 @@ static std::vector<BlockShape> class_shapes(const tamm_group* g, int layout, dou
   return shapes;
 }
 
-// Default configuration of the nodes of one layout class: the least estimated time of its launch.
-static int group_default_config(const tamm_group* g, int layout) {
+// Default configuration of the nodes of one layout class, and whether long items are cut: the least
+// estimated time of its launch.
+static int group_default_config(const tamm_group* g, int layout, bool* cut) {
   double bytes = 0;
   const std::vector<BlockShape> shapes = class_shapes(g, layout, &bytes);
   int config = 0;
   double best = 1e300;
   for (int c = 0; c < f64_config_count(); ++c) {
     if (f64_config_canonical(c) != c) continue;
-    const double t = group_estimate_us(shapes, cfg_get(TAMM_PREC_F64, c), bytes);
-    if (t < best) {
-      best = t;
-      config = c;
+    for (bool with_cut : {true, false}) {
+      const double t = group_estimate_us(shapes, cfg_get(TAMM_PREC_F64, c), bytes, with_cut);
+      if (t < best) {
+        best = t;
+        config = c;
+        *cut = with_cut;
+      }
     }
   }
   return config;
 }
 
 // Work lists of every layout class with the class's configuration cfgs[c] (< 0: the class's
-// default), each heaviest first, and the workspace layout.
+// default; others cut long items), each heaviest first, and the workspace layout.
 static int group_configure_classes(tamm_group* g, const int* cfgs, const int* grids) {
+  bool cut[kLayouts];
+  std::fill(cut, cut + kLayouts, true);
   for (int c = 0; c < kLayouts; ++c) {
-    const int k = cfgs[c] < 0 ? group_default_config(g, c) : cfgs[c];
+    const int k = cfgs[c] < 0 ? group_default_config(g, c, &cut[c]) : cfgs[c];
     if (k >= f64_config_count()) return fail(TAMM_ERR_ARG, "configuration %d does not exist", k);
     g->cfg[c] = k;
   }
@@ -1816,7 +1874,7 @@ static int group_configure_classes(tamm_group* g, const int* cfgs, const int* gr
     std::vector<int32_t> cm, cn;
     const TileCfg tc = cfg_get(TAMM_PREC_F64, g->cfg[c]);
     double bytes = 0;
-    const double limit = group_limit_us(class_shapes(g, c, &bytes), tc);
+    const double limit = cut[c] ? group_limit_us(class_shapes(g, c, &bytes), tc) : 1e300;
     for (size_t q = 0; q < g->nodes.size(); ++q) {
       if (node_layout(g, q) != c) continue;
       const tamm_plan* p = g->nodes[q][0];
