@@ -523,11 +523,13 @@ TAMM_F64_KERNELS(TAMM_F64_ENTRY)
 #undef TAMM_F64_ENTRY
 
 // Configuration ids, as tuning files hold them.  Ids whose own tile shape became a size of another
-// kernel's tiles (80 and 256 wide, 128 x 128 at one wave per SIMD) name the kernel that runs them.
+// kernel's tiles (80 and 256 wide, 128 x 128 at one wave per SIMD or in chunks of 32) name the kernel
+// that runs them; a new kernel takes a new id.
 static const F64Kernel* const kF64Configs[] = {
     &kF64_m64n64k16,  &kF64_m128n64k16, &kF64_m64n128k16, &kF64_m128n128k16, &kF64_m32n64k16,
     &kF64_m128n64k16, &kF64_m64n128k16, &kF64_m64n64k16,  &kF64_m64n128k16,  &kF64_m128n64k16,
-    &kF64_m32n32k16,  &kF64_m128n64k16, &kF64_m64n80k32,  &kF64_m64n64k32,   &kF64_m128n128k16};
+    &kF64_m128n128k16, &kF64_m128n64k16, &kF64_m64n80k32, &kF64_m64n64k32,   &kF64_m128n128k16,
+    &kF64_m32n32k16};
 
 int f64_config_count() { return (int)(sizeof(kF64Configs) / sizeof(kF64Configs[0])); }
 const F64Config& f64_config(int id) { return kF64Configs[id]->cfg; }
