@@ -200,7 +200,8 @@ typedef struct {
   int32_t xcd_chunk;      /* launch order over the eight dies: work items per die chunk (0: the
                              plain longest-first order); see tamm_plan_set_order                */
   int32_t tile_order;     /* 0: the tiles of a block row by row; 1: grouped by B column panel  */
-  int32_t reserved;       /* zero                                                              */
+  int32_t persistent;     /* 1: float64 launch of long items whose workgroups are resident and
+                             take items from their die's queue; 0: one workgroup per item       */
 } tamm_plan_stats;
 
 int tamm_plan_stats_get(const tamm_plan* p, tamm_plan_stats* s);

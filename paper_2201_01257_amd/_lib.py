@@ -31,7 +31,7 @@ class PlanStats(ctypes.Structure):
         ("gather_layout", c_i32),
         ("xcd_chunk", c_i32),
         ("tile_order", c_i32),
-        ("reserved", c_i32),
+        ("persistent", c_i32),
     ]
 
 

@@ -1111,6 +1111,7 @@ static int configure_work(tamm_plan* p, int config, int k_splits) {
   p->stats.xcd_chunk = p->xcd_chunk >= 0 ? p->xcd_chunk : xcd_chunk();
   p->stats.tile_order = p->tile_order;
   p->stats.gather_layout = gather_layout(p);
+  p->stats.persistent = p->queued ? 1 : 0;
   layout_workspace(p, f, p->work.size(), p->reduce.size(), (size_t)slots, p->queued);
   p->ws_bound = false;
   p->screened = false;

@@ -1,8 +1,10 @@
 """Launches of one plan that overlap: on more streams than the plan has counter sets, with partial sums
 of K splits, and in captured graphs (more of them than there are sets for) beside eager launches, each
-with an output of its own.  Every output must hold the bits that the plan writes alone.  And the order
-of capture and first execution of a group."""
+with an output of its own.  Every output must hold the bits that the plan writes alone.  Launches over the
+dies' queues with every tile size, with K splits and on a group's own grid.  And the order of capture and
+first execution of a group."""
 
+import numpy as np
 import pytest
 import torch
 
@@ -21,6 +23,7 @@ def long_plan(k_tiles=(200, 56), k_splits=1):
         t.data.copy_(torch.randn(t.data.shape, dtype=torch.float64, device="cuda", generator=g))
     plan = tm.Plan(C, "ij", A, "ik", B, "kj")
     plan.set_config(3, k_splits)
+    assert plan.stats()["persistent"] == (1 if sum(k_tiles) // k_splits >= 256 else 0)
     plan.execute(1.0, 0.0)
     torch.cuda.synchronize()
     want = C.data.clone()
@@ -78,6 +81,53 @@ def test_contractions_after_one_screening():
         plan.contract(1.0, 0.0)
         torch.cuda.synchronize()
         assert torch.equal(C.data, want)
+
+
+# (configuration, K splits): whether the launch takes its items from the queues (more items than resident
+# workgroups, 40 us and more each)
+@pytest.mark.parametrize("config,k_splits,persistent", [(3, 1, 1), (1, 1, 1), (2, 1, 1), (0, 1, 1), (4, 1, 1), (12, 1, 1), (13, 1, 1),
+                                                        (15, 1, 1), (3, 2, 1), (1, 2, 1), (1, 3, 0)])
+def test_queues_with_every_tile_size_and_splits(config, k_splits, persistent):
+    m, n, k = tm.Space.explicit([1530, 1517]), tm.Space.explicit([1290, 1803]), tm.Space.explicit([300, 301, 299])
+    A, B, C = tm.Tensor([m, k]), tm.Tensor([k, n]), tm.Tensor([m, n])
+    g = torch.Generator(device="cuda").manual_seed(5)
+    for t in (A, B, C):
+        t.data.copy_(torch.randn(t.data.shape, dtype=torch.float64, device="cuda", generator=g))
+    a, b, c0 = (t.to_dense() for t in (A, B, C))
+    plan = tm.Plan(C, "ij", A, "ik", B, "kj")
+    plan.set_config(config, k_splits)
+    assert plan.stats()["persistent"] == persistent
+    for _ in range(2):
+        plan.execute(0.5, 1.0)
+    torch.cuda.synchronize()
+    # a sum of K products in another order: 2 (K + 2) u of the sum of magnitudes, for each of two executions
+    err, bound = np.abs(C.to_dense() - (a @ b + c0)), 4 * (a.shape[1] + 2) * 2.0 ** -53 * (np.abs(a) @ np.abs(b) + np.abs(c0))
+    assert (err <= bound).all()
+
+
+@pytest.mark.parametrize("grid", [1, 7, 100])
+def test_group_on_a_grid_of_fewer_workgroups_than_items(grid):
+    m, k = tm.Space.explicit([200, 171]), tm.Space.explicit([16, 40])
+    plans = []
+    for (sa, la), (sb, lb) in ((([m, k], "ik"), ([k, m], "kj")), (([k, m], "ki"), ([m, k], "jk"))):
+        A, B, C = tm.Tensor(sa), tm.Tensor(sb), tm.Tensor([m, m])
+        for t in (A, B):
+            t.data.normal_()
+        plans.append(tm.Plan(C, "ij", A, la, B, lb, bind=False))
+    group = tm.Group(plans)
+    group.set_config(15)
+    group.execute([1.0, 1.0], [0.0, 0.0])
+    torch.cuda.synchronize()
+    want = [p.out.data.clone() for p in plans]
+    group.set_config(15, grid)
+    assert group.stats()["work_items"] > 2 * grid
+    for _ in range(2):
+        for p in plans:
+            p.out.data.fill_(float("nan"))
+        group.execute([1.0, 1.0], [0.0, 0.0])
+        torch.cuda.synchronize()
+        for p, w in zip(plans, want):
+            assert torch.equal(p.out.data, w)
 
 
 def test_group_of_several_layouts_is_executed_before_it_is_captured():
