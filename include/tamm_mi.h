@@ -197,8 +197,8 @@ typedef struct {
                              precisions store the split operands as slice planes, each block
                              [row][k], because every operand block's K extent is a multiple
                              of 8 (16-byte gathers of 8 slices)                              */
-  int32_t xcd_chunk;      /* launch order over the eight dies: work items per die chunk (0: the
-                             plain longest-first order); see tamm_plan_set_order                */
+  int32_t xcd_chunk;      /* launch order over the eight dies: work items per die chunk (0: one
+                             by one, longest first); see tamm_plan_set_order                    */
   int32_t tile_order;     /* 0: the tiles of a block row by row; 1: grouped by B column panel  */
   int32_t persistent;     /* 1: float64 launch of long items whose workgroups are resident and
                              take items from their die's queue; 0: one workgroup per item       */
@@ -219,12 +219,12 @@ int tamm_plan_set_config(tamm_plan* p, int32_t config, int32_t k_splits);
  * longest first; among tiles of equal cost, tile_order 0 keeps the tiles of one output block
  * together, row by row (neighbours share A row panels), and tile_order 1 groups the tiles that
  * read the same B column panel across blocks and rows.  Then the list is cut into chunks of
- * `chunk` items for the chip's eight dies (each with its own L2), chunk c running on die c mod 8
- * (in a float64 launch of long items, by default: its workgroups are resident and take items from
- * their own die's queue, then from the others');
- * 0 keeps the list as it is; -1 restores the library default (32, or the TAMM_XCD_CHUNK
- * environment variable).  The autotuner searches both after the kernel configuration.  Requires
- * re-binding. */
+ * `chunk` items for the chip's eight dies (each with its own L2), chunk c running on die c mod 8.
+ * In a persistent launch (tamm_plan_stats.persistent) the chunks of a die are its queue: its
+ * workgroups take items from it, then from the others'.  A chunk of 0 keeps the list as it is, which
+ * deals the items one by one over the dies, as 1 does; -1 restores the library default (32, or
+ * the TAMM_XCD_CHUNK environment variable).  The autotuner searches both after the kernel
+ * configuration.  Requires re-binding. */
 int tamm_plan_set_order(tamm_plan* p, int32_t tile_order, int32_t chunk);
 /* Declare operand `which` (0 = lhs, 1 = rhs) constant (constant != 0) or variable.  For the
  * split-bfloat16 precisions the split of a constant operand, made by the first execution, is
@@ -359,10 +359,9 @@ int tamm_group_workspace_size(const tamm_group* g, size_t* bytes);
  * (synchronous).  Drops a captured graph. */
 int tamm_group_bind_workspace(tamm_group* g, void* dev_ptr, size_t bytes);
 /* Select one kernel configuration for every class (-1 = each class's default: the least estimated
- * time)
- * and the persistent grid size (0 = every resident slot: compute units x workgroups of the
- * configuration that fit on one).  Requires re-binding (the workspace size does not depend on
- * the configuration). */
+ * time) and the persistent grid size (0 = every resident slot, compute units x workgroups of the
+ * configuration that fit on one, for classes of long items, and one workgroup per item for others).
+ * Requires re-binding (the workspace size does not depend on the configuration). */
 int tamm_group_set_config(tamm_group* g, int32_t config, int32_t grid);
 /* alpha and beta are host arrays of n values, read during the call.  If a graph was captured
  * with the same alpha/beta and the members' storage bindings are unchanged, the graph is

@@ -636,18 +636,12 @@ static TileCfg cfg_get(int prec, int c, bool planes = false) {
   return TileCfg{f.mt, f.nt, f.kt, 64 * f.wgm * f.wgn, f.mt, f.nt, f.resident, rate, f.name};
 }
 
-// Number of output tiles and padding factor of one configuration.
-static std::pair<int64_t, double> tiles_for(const tamm_plan* p, int c) {
+// Number of output tiles of one configuration.
+static int64_t tiles_for(const tamm_plan* p, int c) {
   const TileCfg f = cfg_get(p->prec, c);
   int64_t n = 0;
-  double area = 0, useful = 0;
-  for (const auto& b : p->blocks) {
-    const int64_t tm = (b.mext + f.mt - 1) / f.mt, tn = (b.next + f.nt - 1) / f.nt;
-    n += tm * tn;
-    area += (double)tm * f.mt * tn * f.nt;
-    useful += (double)b.mext * b.next;
-  }
-  return std::make_pair(n, useful > 0 ? area / useful : 1.0);
+  for (const auto& b : p->blocks) n += (int64_t)((b.mext + f.mt - 1) / f.mt) * ((b.next + f.nt - 1) / f.nt);
+  return n;
 }
 
 // K splits of a block's tiles: in proportion to its summed K extent, the heaviest blocks' get
@@ -974,7 +968,7 @@ static void xcd_order(std::vector<WorkItem>& work, size_t first, int chunk) {  /
 }
 
 // The same chunks as the queues of a persistent launch: chunk c of the longest-first list goes to
-// queue c % 8, each queue's chunks in list order.  A workgroup takes its next item when it has ended
+// queue c % 8, each queue's chunks in list order (chunks of 0 or 1: item by item).  A workgroup takes its next item when it has ended
 // the last, so unequal items leave no slot empty until the queues run dry; the dispatcher, handing
 // out one workgroup per item in a fixed rotation, kept 76-92 % of the slots busy (ladder at O=40,
 // V=200, K splits 4 and 1).
@@ -1032,7 +1026,7 @@ static int configure_work(tamm_plan* p, int config, int k_splits) {
   if (config >= ncfg) return fail(TAMM_ERR_ARG, "kernel configuration %d does not exist (%d available)", config, ncfg);
   if (config < 0 || k_splits <= 0) std::tie(config, k_splits) = default_work(p, config, k_splits);
   const TileCfg f = cfg_get(p->prec, config);
-  const int64_t ntiles = tiles_for(p, config).first;
+  const int64_t ntiles = tiles_for(p, config);
   if (k_splits > 64) return fail(TAMM_ERR_ARG, "k_splits must be in [1, 64]");
   struct Tile {
     double cost;
@@ -1654,11 +1648,11 @@ extern "C" int tamm_plan_autotune(tamm_plan* p, void* workspace, size_t bytes, v
       return TAMM_OK;
     };
     const int chunk0 = p->xcd_chunk;
-    const int64_t ntiles_max = tiles_for(p, 0).first;
+    const int64_t ntiles_max = tiles_for(p, 0);
     std::vector<CacheEntry> ranked;  // every (configuration, K splits) at the current launch order
     for (int c = 0; c < cfg_count(p->prec) && rc == TAMM_OK; ++c) {
       if (p->prec == TAMM_PREC_F64 && f64_config_canonical(c) != c) continue;  // another id of a kernel already timed
-      const int64_t nt = tiles_for(p, c).first;
+      const int64_t nt = tiles_for(p, c);
       for (int ks : {1, 2, 4, 8}) {
         if (ks > 1 && nt * ks > 4 * std::max<int64_t>(ntiles_max, 2048)) continue;
         float ms = 0;
