@@ -869,13 +869,15 @@ size_t tamm::plan_candidate_workspace(const tamm_plan* p, int max_splits) {
   return most;
 }
 
-// Default configuration and K splits of a plan: the least estimate; more splits only where they are
-// estimated to gain 3 %, never of sums shorter than eight chunks in float64 and float32 (what they gain
-// is what ordering overlapping executions costs, see `starved`: ring at O=5, V=45 16 us in four parts,
-// 19 in one, 20 in four with the event; in split bfloat16 at O=9, V=37 35, 43 and 38), and in float64 8 % above a millisecond, where the queues have filled the tail
-// that splits would (ladder and its gradients at O=32, V=160: 3.1 ms in one part, 3.4 in four).  The partial
-// tiles take at most an eighth of the tensors' bytes or 64 MiB, and the whole workspace no more than the
-// plan's limit.
+// Default configuration and K splits of a plan: the least estimate.  More splits only where they are
+// estimated to gain 3 %, and in float64 8 % above a millisecond: of long launches the estimate tells the
+// splits that gain from those that lose too poorly, since the dies' queues fill part of the tail (128 x 128
+// tiles in 1, 2 and 4 parts: ladder at O=40, V=200 13.1, 12.6 and 13.3 ms; at O=32, V=160 3.07, 3.11 and
+// 3.38, its gradients 3.26, 4.22 and 8.26 and 3.09, 3.12 and 3.45; ring at O=40, V=200 2.49, 2.66 and 2.73).
+// Never of sums shorter than eight chunks in float64 and float32: what they gain is what ordering
+// overlapping executions costs, see `starved` (ring at O=5, V=45 16 us in four parts, 19 in one, 20 in four
+// with the event; in split bfloat16 at O=9, V=37 35, 43 and 38).  The partial tiles take at most an eighth
+// of the tensors' bytes or 64 MiB, and the whole workspace no more than the plan's limit.
 static std::pair<int, int> default_work(const tamm_plan* p, int config, int k_splits) {
   const bool f64 = p->prec == TAMM_PREC_F64, split_bf16 = !f64 && p->prec != TAMM_PREC_F32;
   const double bytes = p->stats.algorithmic_bytes, budget = std::max(bytes / 8, (double)(64 << 20));
