@@ -522,14 +522,13 @@ struct F64Kernel {
 TAMM_F64_KERNELS(TAMM_F64_ENTRY)
 #undef TAMM_F64_ENTRY
 
-// Configuration ids, as tuning files hold them.  Ids whose own tile shape became a size of another
-// kernel's tiles (80 and 256 wide, 128 x 128 at one wave per SIMD or in chunks of 32) name the kernel
-// that runs them; a new kernel takes a new id.
+// Configuration ids, as tuning files hold them; their number is fixed.  Ids whose own tile shape became a
+// size of another kernel's tiles (80 and 256 wide, 128 x 128 at one wave per SIMD or in chunks of 32) name
+// the kernel that runs them; 9, once 256 x 32 for outputs of few columns, names the 32 x 32 kernel.
 static const F64Kernel* const kF64Configs[] = {
-    &kF64_m64n64k16,  &kF64_m128n64k16, &kF64_m64n128k16, &kF64_m128n128k16, &kF64_m32n64k16,
-    &kF64_m128n64k16, &kF64_m64n128k16, &kF64_m64n64k16,  &kF64_m64n128k16,  &kF64_m128n64k16,
-    &kF64_m128n128k16, &kF64_m128n64k16, &kF64_m64n80k32, &kF64_m64n64k32,   &kF64_m128n128k16,
-    &kF64_m32n32k16};
+    &kF64_m64n64k16,   &kF64_m128n64k16, &kF64_m64n128k16, &kF64_m128n128k16, &kF64_m32n64k16,
+    &kF64_m128n64k16,  &kF64_m64n128k16, &kF64_m64n64k16,  &kF64_m64n128k16,  &kF64_m32n32k16,
+    &kF64_m128n128k16, &kF64_m128n64k16, &kF64_m64n80k32,  &kF64_m64n64k32,   &kF64_m128n128k16};
 
 int f64_config_count() { return (int)(sizeof(kF64Configs) / sizeof(kF64Configs[0])); }
 const F64Config& f64_config(int id) { return kF64Configs[id]->cfg; }

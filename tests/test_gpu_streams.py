@@ -86,7 +86,7 @@ def test_contractions_after_one_screening():
 # (configuration, K splits): whether the launch takes its items from the queues (more items than resident
 # workgroups, 40 us and more each)
 @pytest.mark.parametrize("config,k_splits,persistent", [(3, 1, 1), (1, 1, 1), (2, 1, 1), (0, 1, 1), (4, 1, 1), (12, 1, 1), (13, 1, 1),
-                                                        (15, 1, 1), (3, 2, 1), (1, 2, 1), (1, 3, 0)])
+                                                        (9, 1, 1), (3, 2, 1), (1, 2, 1), (1, 3, 0)])
 def test_queues_with_every_tile_size_and_splits(config, k_splits, persistent):
     m, n, k = tm.Space.explicit([1530, 1517]), tm.Space.explicit([1290, 1803]), tm.Space.explicit([300, 301, 299])
     A, B, C = tm.Tensor([m, k]), tm.Tensor([k, n]), tm.Tensor([m, n])
@@ -115,11 +115,11 @@ def test_group_on_a_grid_of_fewer_workgroups_than_items(grid):
             t.data.normal_()
         plans.append(tm.Plan(C, "ij", A, la, B, lb, bind=False))
     group = tm.Group(plans)
-    group.set_config(15)
+    group.set_config(9)
     group.execute([1.0, 1.0], [0.0, 0.0])
     torch.cuda.synchronize()
     want = [p.out.data.clone() for p in plans]
-    group.set_config(15, grid)
+    group.set_config(9, grid)
     assert group.stats()["work_items"] > 2 * grid
     for _ in range(2):
         for p in plans:
