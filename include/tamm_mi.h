@@ -487,7 +487,9 @@ int tamm_add_destroy(tamm_add* a);
  * tamm_sched_execute: enqueue every level on stream.  If a graph was captured and every tensor
  *   and energy array is still bound to the same storage, the graph is replayed; otherwise the
  *   launches are issued directly (descriptor refreshes synchronise the stream when bindings moved).
- * tamm_sched_capture: record the whole schedule into one hipGraph (no memset or copy nodes).
+ * tamm_sched_capture: record the whole schedule into one hipGraph (no memset or copy nodes); a
+ *   schedule whose contractions of one level have several gather layouts must have been launched
+ *   before (see tamm_group_capture).
  * tamm_sched_info: levels, nodes, and operations inside fused nodes; tamm_sched_op_info: level and
  *   node of queued operation `op` (0-based, queue order).
  * ------------------------------------------------------------------------------------------ */
